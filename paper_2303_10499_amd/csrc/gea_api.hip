@@ -375,7 +375,7 @@ size_t carve(Carver& cv, gea_ctx* x, const gea_mesh& m, bool learned, bool trans
   x->q132 = cv.take<float>(nc);
   x->d32 = cv.take<float>(nc);
   {
-    const int zb = 3 * zplan(make_geo(m)).blocks;  // partials of the correction kernel
+    const int zb = 3 * zmax_blocks(zplan(make_geo(m)));  // partials of the correction kernel
     x->partials = cv.take<double>(zb > kMaxPartials ? zb : kMaxPartials);
   }
   x->o_part = cv.take<double>(kMaxPartials);
@@ -394,8 +394,9 @@ size_t carve(Carver& cv, gea_ctx* x, const gea_mesh& m, bool learned, bool trans
   // partials: 7 per workgroup of the iteration kernel's grid, in two sets
   // (by iteration parity); 2 (and 1 for ||b||^2) per workgroup of the set-up
   // kernels' column-tile grid
-  const int ns = std::max(iter_grid<double>(make_geo(m)), iter_grid<float>(make_geo(m)));
-  const int nzb = zplan(make_geo(m)).blocks;
+  const Geo G = make_geo(m);
+  const int ns = std::max({iter_grid<double>(G), iter_grid<double>(G, true), iter_grid<float>(G)});
+  const int nzb = zmax_blocks(zplan(make_geo(m)));
   for (CgWork* w : {&x->w64, &x->w32}) {
     w->s = cv.take<double>(14 * (size_t)ns);
     w->u[0] = nullptr;
@@ -410,8 +411,8 @@ size_t carve(Carver& cv, gea_ctx* x, const gea_mesh& m, bool learned, bool trans
   x->z32 = cv.take<float>(nc);
   x->pair_part = cv.take<double>(3 * 2048);
   x->pair_s = cv.take<double>(2);
-  x->fv.part_d = cv.take<double>(4 * (size_t)std::max(2048, zplan(make_geo(m)).blocks));  // (4 sums a workgroup at the hand-over)
-  x->fv.part_s = cv.take<double>(2 * (size_t)std::max(2048, zplan(make_geo(m)).blocks));
+  x->fv.part_d = cv.take<double>(4 * (size_t)std::max(2048, nzb));  // (4 sums a workgroup at the hand-over)
+  x->fv.part_s = cv.take<double>(2 * (size_t)std::max(2048, nzb));
   x->fv.part_u = cv.take<double>(2 * 2048);
   // the network (inference buffers) only for the learned form on a mesh whose
   // dimensions are multiples of 4
@@ -1077,7 +1078,8 @@ gea_status solve(gea_ctx* x, double* xv, gea_solve_stats* out) {
 // FP64 on (c, D = (mu/Pr) c_p, 1/diag, b) from the initial guess in T, to kEnergyTol.
 gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters) {
   const Geo& G = x->G;
-  const CgWork& w = x->w64;
+  CgWork w = x->w64;
+  w.ns = iter_grid<double>(G, true);
   // D = (mu/Pr) c_p in every cell: the iteration kernels take it as a value
   // and form 1/diag from c (no 1/diag array)
   CgVectors<double> v{T, x->r, x->r1, x->p0, x->p1, x->q, x->q1, x->c, nullptr, nullptr, x->b,
@@ -1116,6 +1118,7 @@ gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters
 TrOp momentum_op(const gea_ctx* x, const State& S, int comp) {
   const Geo& G = x->G;
   TrOp op{};
+  op.fixed_order = x->prm.solver != GEA_PCG_JACOBI_FP64;
   op.rho_star = x->rho_star;
   op.tcoef = G.V / x->ph.dt;
   op.gamma = 1.0;
@@ -1130,6 +1133,7 @@ TrOp momentum_op(const gea_ctx* x, const State& S, int comp) {
 TrOp energy_op(const gea_ctx* x, const State& S, bool enth) {
   const Geo& G = x->G;
   TrOp op{};
+  op.fixed_order = x->prm.solver != GEA_PCG_JACOBI_FP64;
   op.rho_star = x->rho_star;
   op.tcoef = (enth ? x->ph.cp : x->ph.cv) * G.V / x->ph.dt;
   op.gamma = x->ph.cp;
@@ -1146,7 +1150,7 @@ TrOp energy_op(const gea_ctx* x, const State& S, bool enth) {
 gea_status bicg_run(gea_ctx* x, const TrOp& op, double* xv, int* iters) {
   const Geo& G = x->G;
   x->timer.run(7, x->stream, [&] {
-    launch_tr_start(x->stream, G, x->partials, kTransportTol, x->prm.max_iter, x->tsc);
+    launch_tr_start(x->stream, G, op, x->partials, kTransportTol, x->prm.max_iter, x->tsc);
   });
   TrScalars hs{};
   int batch = 2;

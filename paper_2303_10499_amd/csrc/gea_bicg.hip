@@ -452,9 +452,11 @@ __global__ __launch_bounds__(kBlock) void k_tr_end(const double* part, int nb, T
 
 // ---- launchers ---------------------------------------------------------------
 
+static ZPlan tr_plan(const Geo& G, const TrOp& op) { return op.fixed_order ? zplan_fixed(G) : zplan(G); }
+
 void launch_tr_setup_mom(hipStream_t s, const Geo& G, const TrOp& op, const double* x0,
                          const TrVecs& v, double* part) {
-  const ZPlan zp = zplan(G);
+  const ZPlan zp = tr_plan(G, op);
   if (G.ndim == 2)
     hipLaunchKernelGGL(k_tr_setup_mom<2>, dim3(zp.blocks), dim3(kBlock), 0, s, G, zp.kc, dev_op<2>(op), x0, v, part);
   else
@@ -466,7 +468,7 @@ void launch_tr_setup_energy(hipStream_t s, const Geo& G, const Phys& ph, bool en
                             double* w, const double* Tn, const double* Tbg, double* x,
                             const TrVecs& v, double* part) {
   const int gb = grid_for(G.nc);
-  const ZPlan zp = zplan(G);
+  const ZPlan zp = tr_plan(G, op);
   if (G.ndim == 2) {
     hipLaunchKernelGGL(k_tr_known<2>, dim3(gb), dim3(kBlock), 0, s, G, ph, uvec<2>(u_star), (int)enth, w);
     if (enth)
@@ -482,15 +484,15 @@ void launch_tr_setup_energy(hipStream_t s, const Geo& G, const Phys& ph, bool en
   }
 }
 
-void launch_tr_start(hipStream_t s, const Geo& G, const double* part, double tol, int max_iter,
+void launch_tr_start(hipStream_t s, const Geo& G, const TrOp& op, const double* part, double tol, int max_iter,
                      TrScalars* sc) {
-  hipLaunchKernelGGL(k_tr_start, dim3(1), dim3(kBlock), 0, s, part, zplan(G).blocks, tol, max_iter, sc);
+  hipLaunchKernelGGL(k_tr_start, dim3(1), dim3(kBlock), 0, s, part, tr_plan(G, op).blocks, tol, max_iter, sc);
 }
 
 void launch_tr_iteration(hipStream_t s, const Geo& G, const TrOp& op, double* x, const TrVecs& v,
                          double* part, TrScalars* sc) {
   const int gb = grid_for(G.nc);
-  const ZPlan zp = zplan(G);
+  const ZPlan zp = tr_plan(G, op);
   const dim3 grid(gb), block(kBlock), zgrid(zp.blocks);
   const TrScalars* csc = sc;
   hipLaunchKernelGGL(k_tr_dir, grid, block, 0, s, G.nc, v, csc);

@@ -54,9 +54,20 @@ namespace {
 
 constexpr int kTX3 = 64, kTY3 = 8;  // 3D tile
 constexpr int kFoldMaxParts = 512;   // largest iteration grid that folds its scalars
-// z chunk of the 3D iteration kernel
+// z chunk of the 3D iteration kernel, at most
 template <typename T>
 constexpr int kKC3 = sizeof(T) == 8 ? 64 : 32;
+// and on the mesh at hand: shorter where those chunks would leave CUs idle
+// (one 256-thread workgroup a CU in FP64, two in FP32: the counts at which
+// the chunk lengths above were measured)
+// (cd: the energy solves', whose sums keep one order on every mesh, see
+// zplan_fixed)
+template <typename T>
+ZPlan plan3(const Geo& G, bool cd) {
+  const int cols = ((G.nx + kTX3 - 1) / kTX3) * ((G.ny + kTY3 - 1) / kTY3);
+  if (cd) return ZPlan{kKC3<T>, cols * ((G.nz + kKC3<T> - 1) / kKC3<T>), kKC3<T>};
+  return chunk_plan(cols, G.nz, kKC3<T>, sizeof(T) == 8 ? 1 : 2);
+}
 constexpr int kTX2 = 256;  // 2D row segment
 // z chunk of the 2D iteration kernel
 template <typename T>
@@ -359,8 +370,8 @@ __device__ __forceinline__ void st_stream(T v, T* p) {
 }
 
 // 3D iteration kernel: a workgroup owns a 64 x 8 column tile and marches it
-// through a chunk of planes (32 in FP32, 64 in FP64, whose loads carry twice
-// the bytes).  Thread t stages its two own cells (t % 64, t / 64) and
+// through a chunk of KC planes (up to 32 in FP32, 64 in FP64, whose loads carry
+// twice the bytes; see plan3).  Thread t stages its two own cells (t % 64, t / 64) and
 // (t % 64, t / 64 + 4) and, for t < 148, one halo cell of the tile; each
 // staged plane is loaded into registers ahead (two planes in FP32, one in
 // FP64: old residual, old A p, old direction, D, 1/diag), turned into the new residual
@@ -374,8 +385,8 @@ __device__ __forceinline__ void st_stream(T v, T* p) {
 // of 1/diag and no 1/diag array is read
 template <typename T, bool CD>
 __global__ __launch_bounds__(kBlock) void k_cg_iter3(Geo G, Stencil<3, T> K, CgIter<T> v,
-                                                     CgStep stp, CgScalars* sc) {
-  constexpr int TX = kTX3, TY = kTY3, KC = kKC3<T>;
+                                                     int KC, CgStep stp, CgScalars* sc) {
+  constexpr int TX = kTX3, TY = kTY3;
   constexpr int HX = TX + 2, HY = TY + 2, HP = HX * HY;
   constexpr int RPT = TX * TY / kBlock;  // own cells per thread
   constexpr int NH = HP - TX * TY;       // halo cells of a plane
@@ -947,13 +958,12 @@ Stencil<NDIM, T> stencil(const Geo& G) {
 }  // namespace
 
 template <typename T>
-int iter_grid(const Geo& G) {
-  if (G.ndim == 3)
-    return ((G.nx + kTX3 - 1) / kTX3) * ((G.ny + kTY3 - 1) / kTY3) * ((G.nz + kKC3<T> - 1) / kKC3<T>);
+int iter_grid(const Geo& G, bool cd) {
+  if (G.ndim == 3) return plan3<T>(G, cd).blocks;
   return ((G.nx + kTX2 - 1) / kTX2) * ((G.nz + kKC2<T> - 1) / kKC2<T>);
 }
-template int iter_grid<double>(const Geo&);
-template int iter_grid<float>(const Geo&);
+template int iter_grid<double>(const Geo&, bool);
+template int iter_grid<float>(const Geo&, bool);
 
 template <typename T>
 void cg_init(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgWork& w, double tol,
@@ -992,14 +1002,14 @@ void cg_iter_kernel(hipStream_t s, const Geo& G, const CgVectors<T>& v, int iter
   const bool cd = v.D == nullptr;
   if (G.ndim == 2) {
     if (cd)
-      hipLaunchKernelGGL((k_cg_iter2<T, true>), dim3(iter_grid<T>(G)), dim3(kBlock), 0, s, G, stencil<2, T>(G), it, stp, w.sc);
+      hipLaunchKernelGGL((k_cg_iter2<T, true>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<2, T>(G), it, stp, w.sc);
     else
-      hipLaunchKernelGGL((k_cg_iter2<T, false>), dim3(iter_grid<T>(G)), dim3(kBlock), 0, s, G, stencil<2, T>(G), it, stp, w.sc);
+      hipLaunchKernelGGL((k_cg_iter2<T, false>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<2, T>(G), it, stp, w.sc);
   } else {
     if (cd)
-      hipLaunchKernelGGL((k_cg_iter3<T, true>), dim3(iter_grid<T>(G)), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, stp, w.sc);
+      hipLaunchKernelGGL((k_cg_iter3<T, true>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, plan3<T>(G, cd).kc, stp, w.sc);
     else
-      hipLaunchKernelGGL((k_cg_iter3<T, false>), dim3(iter_grid<T>(G)), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, stp, w.sc);
+      hipLaunchKernelGGL((k_cg_iter3<T, false>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, plan3<T>(G, cd).kc, stp, w.sc);
   }
 }
 

@@ -9,6 +9,7 @@ namespace gea {
 
 constexpr int kBlock = 256;     // threads per workgroup (4 waves of 64)
 constexpr int kMaxDim = 3;
+constexpr int kCus = 256;       // compute units of the card
 
 // Uniform hexahedral mesh.  Direction d = 0..ndim-1 is x, (y,) z; z is the
 // last direction.  Index P = i + nx*(j + ny*k).
@@ -68,11 +69,24 @@ constexpr int kMaxZBlocks = 4096;
 struct ZPlan {
   int kc;
   int blocks;
+  int kf;  // length of the full chunks that kc cuts (see chunk_plan)
 };
+// upper bound of the workgroups of every plan on the mesh (partials' space)
+inline int zmax_blocks(const ZPlan& zp) { return zp.blocks > kMaxZBlocks ? zp.blocks : kMaxZBlocks; }
 ZPlan zplan(const Geo& G);
+ZPlan chunk_plan(int cols, int nz, int kc0, int per);
+// The same tiles in chunks whose length does not follow the mesh's fill of
+// the card (kRowSegments marks the 2D row segments in kc): the order of the
+// sums that kernels launched so form along a chunk is that of large meshes.
+// The refined forms' transport and energy solves use it: their FP32 inner
+// solves start from a residual in which the state's last bits show, and a
+// last bit of T moved by another order of summation parts two runs by the
+// FP32 rounding of the correction (1e-9 of the face flux after four steps of
+// a 64 x 64 x 32 mesh).
+constexpr int kRowSegments = 1 << 20;
+ZPlan zplan_fixed(const Geo& G);
 // 3D column tiles of 64 x ty cells (64 ty threads a workgroup) marching
-// chunks of kc planes (fewer chunks where zplan would need them); never more
-// workgroups than zplan's for ty >= 4 and kc >= its chunk
+// chunks of at most kc planes; never more workgroups than zmax_blocks
 ZPlan zplan3(const Geo& G, int ty, int kc);
 
 // ---- explicit step kernels (gea_step.hip) ----------------------------------
@@ -211,8 +225,9 @@ struct CgWork {
   CgScalars* sc;
 };
 
+// workgroups of the CG iteration kernel in precision T (cd: CgVectors::D null)
 template <typename T>
-int iter_grid(const Geo& G);  // workgroups of the CG iteration kernel in precision T
+int iter_grid(const Geo& G, bool cd = false);
 template <typename T>
 void cg_init(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgWork& w, double tol,
              int max_iter);
@@ -267,6 +282,7 @@ void launch_fill(hipStream_t s, const Geo& G, double* a, double v);
 // Operator (times V): (A x)_P = rho*_P tcoef x_P + gamma sum_out phi I4(x)
 //   + sum_f k_d (x_P - x_nb) + 2 k_d x_P on the walls normal to d = wall_comp.
 struct TrOp {
+  bool fixed_order;  // chunks of zplan_fixed
   const double* rho_star;
   double tcoef;
   const double* phi[3];
@@ -292,7 +308,7 @@ void launch_tr_setup_energy(hipStream_t s, const Geo& G, const Phys& ph, bool en
                             const double* rho, const double* e0, double* const* u_star,
                             double* w, const double* Tn, const double* Tbg, double* x,
                             const TrVecs& v, double* part);
-void launch_tr_start(hipStream_t s, const Geo& G, const double* part, double tol, int max_iter,
+void launch_tr_start(hipStream_t s, const Geo& G, const TrOp& op, const double* part, double tol, int max_iter,
                      TrScalars* sc);
 // one BiCGStab iteration (nine launches; all return at once once sc->done)
 void launch_tr_iteration(hipStream_t s, const Geo& G, const TrOp& op, double* x, const TrVecs& v,

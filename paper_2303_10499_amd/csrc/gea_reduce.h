@@ -116,14 +116,16 @@ __device__ __forceinline__ int xcd_block() {
 
 // ---- z-marching column tiles ----------------------------------------------------
 //
-// A workgroup owns a TX x TY column of cells (TX cells of one row in 2D) and
-// marches it through kc consecutive planes along z; each thread walks one
+// A workgroup owns a TX x TY column of cells (in 2D each of its waves 64 cells
+// of a row) and marches it through kc consecutive planes along z; each thread walks one
 // vertical column.  Values along z stay in registers (a short queue shifted
 // once per plane), the flux through the face below a cell is the one the
 // same thread formed one plane earlier, and x/y neighbours come from the
 // caches: the workgroup's own rows and the halo rows of the neighbouring
 // columns, which the XCD-aware block order keeps on the same XCD.
 
+// KC: planes of a chunk on a mesh large enough to fill the card with them
+// (shorter on smaller ones, see zplan).
 template <int NDIM>
 struct ZTile;
 template <>
@@ -132,7 +134,7 @@ struct ZTile<3> {
 };
 template <>
 struct ZTile<2> {
-  static constexpr int TX = 256, TY = 1, KC = 8;
+  static constexpr int KC = 8;
 };
 
 struct Col {
@@ -143,21 +145,34 @@ struct Col {
   bool act;      // inside the mesh
 };
 
+// 2D: columns do not exchange anything, so each wave takes a tile of its own
+// (64 columns, one chunk), x fastest: a mesh narrower than 256 cells leaves
+// no wave of a workgroup idle.  A chunk length with kRowSegments set keeps
+// the workgroup's four waves on one 256-cell row segment (see zplan_fixed).
 template <int NDIM>
 __device__ __forceinline__ Col col_of(const Geo& G, int kc) {
-  using T = ZTile<NDIM>;
-  const int ntx = (G.nx + T::TX - 1) / T::TX;
-  const int nty = NDIM == 3 ? (G.ny + T::TY - 1) / T::TY : 1;
-  const int b = xcd_block();
-  const int bx = b % ntx, by = (b / ntx) % nty, bk = b / (ntx * nty);
-  const int nz = G.n[NDIM - 1];
   Col c;
-  c.i = bx * T::TX + (int)threadIdx.x % T::TX;
-  c.j = NDIM == 3 ? by * T::TY + (int)threadIdx.x / T::TX : 0;
-  c.k0 = bk * kc;
+  const int nz = G.n[NDIM - 1];
+  const int b = xcd_block();
+  if constexpr (NDIM == 2) {
+    int ns = (G.nx + 63) / 64;
+    if (kc & kRowSegments) ns = (ns + 3) & ~3;
+    kc &= kRowSegments - 1;
+    const int w = b * (kBlock / 64) + (int)threadIdx.x / 64;
+    c.i = (w % ns) * 64 + (int)threadIdx.x % 64;
+    c.j = 0;
+    c.k0 = min((w / ns) * kc, nz);
+    c.base = c.i;
+  } else {
+    using T = ZTile<NDIM>;
+    const int ntx = (G.nx + T::TX - 1) / T::TX, nty = (G.ny + T::TY - 1) / T::TY;
+    c.i = (b % ntx) * T::TX + (int)threadIdx.x % T::TX;
+    c.j = ((b / ntx) % nty) * T::TY + (int)threadIdx.x / T::TX;
+    c.k0 = (b / (ntx * nty)) * kc;
+    c.base = c.i + G.nx * c.j;
+  }
   c.k1 = min(c.k0 + kc, nz);
   c.pl = G.st[NDIM - 1];
-  c.base = NDIM == 3 ? c.i + G.nx * c.j : c.i;
   c.act = c.i < G.nx && (NDIM == 2 || c.j < G.ny) && c.k0 < nz;
   return c;
 }

@@ -54,6 +54,20 @@ __device__ __forceinline__ double phit_val(double D_lo, double D_hi, double H_lo
   return Df * S * (Hf + phif * (r_hi - r_lo) * inv_h);
 }
 
+// The same with the contraction spelt out, for the 3D kernels: left to the
+// compiler, the last corrector rounded the face below a chunk's first plane
+// otherwise (`fresh`) than a face inside a chunk.  Which faces are rounded so
+// must not follow the chunks that a mesh's fill of the card selects: in
+// k_correct3 they are those at multiples of the plan's full chunk length kf.
+__device__ __forceinline__ double phit3(double D_lo, double D_hi, double H_lo, double H_hi,
+                                        double r_lo, double r_hi, double S, double phif,
+                                        double inv_h, bool fresh = false) {
+  const double Df = 0.5 * (D_lo + D_hi);
+  const double H2 = H_lo + H_hi, g = phif * (r_hi - r_lo);
+  const double in = __builtin_fma(0.5, H2, g * inv_h), fr = __builtin_fma(g, inv_h, 0.5 * H2);
+  return Df * S * (fresh ? fr : in);
+}
+
 // the five staged values of a line through the own cell, stride 1 (x) or HX (y)
 __device__ __forceinline__ Line line_lds(const double* s, int h, int str) {
   return Line{s[h - 2 * str], s[h - str], s[h], s[h + str], s[h + 2 * str]};
@@ -493,6 +507,13 @@ __device__ __forceinline__ Line transported(const Geo& G, const Phys& ph, const 
               one(a.p1, T.p1, kz + d), one(a.p2, T.p2, kz + 2 * d)};
 }
 
+// (c_v + R) T + K* + Phi with Phi rounded before it is added
+__device__ __forceinline__ double centre_energy(const Phys& ph, double Ks, double T, double Phi) {
+#pragma clang fp contract(off)
+  const double h = __builtin_fma(ph.cv + ph.R, T, Ks);
+  return h + Phi;
+}
+
 // ENTH: the enthalpy form (eq. step3_sd): e0 holds the sweep-independent
 // balance q = rho^n c_p T^n + rho^n K^{n-1} - p^{n-1} - rho* K* + p^n
 // - dt rho* g w*, the transported quantity is c_p T^(s-1) + K*, and the
@@ -680,7 +701,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_post(
 // chunks 222 us; 32-plane chunks 225 us.
 template <int TY, bool ENTH, bool KS>
 __global__ __launch_bounds__(64 * TY) void k_energy_rhs3(
-    Geo G, Phys ph, int kc, const double* __restrict__ rho, const double* __restrict__ e0,
+    Geo G, Phys ph, int kc, int kf, const double* __restrict__ rho, const double* __restrict__ e0,
     const double* __restrict__ a_prev, const double* __restrict__ T_prev, Vec<3> phi,
     const double* __restrict__ rho_star, const double* __restrict__ Ks,
     const double* __restrict__ Tbg, EnergySys sy) {
@@ -755,7 +776,11 @@ __global__ __launch_bounds__(64 * TY) void k_energy_rhs3(
     ze.p2 = f1[0][0];
     zT.p2 = f1[1][0];
     const Line Le{ze.m1, ze.c, ze.p1, ze.p2, 0.0}, LT{zT.m1, zT.c, zT.p1, zT.p2, 0.0};  // centred on k0
-    flo = c.k0 > 0 ? phz_lo * i4_lo(hhat(Le, LT, c.k0, true), c.k0, nz) : 0.0;
+    Line L = hhat(Le, LT, c.k0, true);
+    // (a chunk that does not start a full one, see phit3: the value of the
+    // plane below is rounded as the loop rounds its centre plane's)
+    if (KS && !ENTH && c.k0 % kf) L.m1 = centre_energy(ph, Le.m1, LT.m1, phi_cell(G, ph, c.k0 - 1));
+    flo = c.k0 > 0 ? phz_lo * i4_lo(L, c.k0, nz) : 0.0;
   }
   own(c.k0);
   fetch(c.k0 + 2, fs);
@@ -1201,8 +1226,8 @@ __global__ __launch_bounds__(64 * TY) void k_rhs3(Geo G, Phys ph, int kc,
   double hz = H.p[Z][qo + pl * c.k0];  // H_z of the plane computed
   if (c.k0 > 0) {
     const int P = qo + pl * c.k0, Q = P - pl;
-    flux_lo = phit_val(D[Q], D[P], H.p[Z][Q], H.p[Z][P], rho23[Q], rho23[P], G.S[Z],
-                       phi_face<3>(G, ph, Z, c.k0 - 1, c.k0 - 1), G.inv_h[Z]);
+    flux_lo = phit3(D[Q], D[P], H.p[Z][Q], H.p[Z][P], rho23[Q], rho23[P], G.S[Z],
+                    phi_face<3>(G, ph, Z, c.k0 - 1, c.k0 - 1), G.inv_h[Z]);
     diag_lo = 0.5 * (D[Q] + D[P]) * kz_;
     if (RES) {
       xm = xv[Q];
@@ -1245,17 +1270,17 @@ __global__ __launch_bounds__(64 * TY) void k_rhs3(Geo G, Phys ph, int kc,
       const double kd = G.S[d] / G.h[d];
       const double Hc = SH[ho];
       if (q + 1 < G.n[d]) {
-        sum += phit_val(Dc, SD[ho + sd], Hc, SH[ho + sd], r23, Sr[ho + sd], G.S[d], phc, G.inv_h[d]);
+        sum += phit3(Dc, SD[ho + sd], Hc, SH[ho + sd], r23, Sr[ho + sd], G.S[d], phc, G.inv_h[d]);
         diag += 0.5 * (Dc + SD[ho + sd]) * kd;
       }
       if (q > 0) {
-        sum -= phit_val(SD[ho - sd], Dc, SH[ho - sd], Hc, Sr[ho - sd], r23, G.S[d], phc, G.inv_h[d]);
+        sum -= phit3(SD[ho - sd], Dc, SH[ho - sd], Hc, Sr[ho - sd], r23, G.S[d], phc, G.inv_h[d]);
         diag += 0.5 * (SD[ho - sd] + Dc) * kd;
       }
     }
     double flux_hi = 0.0, diag_hi = 0.0;
     if (up) {
-      flux_hi = phit_val(Dc, D_up, Hz, Hz_up, r23, r23_up, G.S[Z], phi_face<3>(G, ph, Z, k, k),
+      flux_hi = phit3(Dc, D_up, Hz, Hz_up, r23, r23_up, G.S[Z], phi_face<3>(G, ph, Z, k, k),
                          G.inv_h[Z]);
       diag_hi = 0.5 * (Dc + D_up) * kz_;
       sum += flux_hi;
@@ -1459,7 +1484,7 @@ __global__ __launch_bounds__(kBlock) void k_correct(
 // flight while a plane is computed.  Same formulas and order as k_correct.
 template <bool LAST, int TY>
 __global__ __launch_bounds__(64 * TY) void k_correct3(
-    Geo G, Phys ph, int kc, const double* __restrict__ pp, const double* __restrict__ rho23,
+    Geo G, Phys ph, int kc, int kf, const double* __restrict__ pp, const double* __restrict__ rho23,
     const double* __restrict__ psi, Vec<3> H, const double* __restrict__ D,
     const double* __restrict__ rho_star, Vec<3> u_out, const double* __restrict__ rho_old,
     double* __restrict__ rho_new, double* __restrict__ p_new, Vec<3> phi_out, double* partials) {
@@ -1507,8 +1532,8 @@ __global__ __launch_bounds__(64 * TY) void k_correct3(
     Flo = force_val(pp[Q], pp[P], rho23[Q], rho23[P], phf, G.inv_h[Z]);
     if (LAST) {
       const double w = 0.5 * (D[Q] + D[P]) * kz_;
-      flux_lo = phit_val(D[Q], D[P], H.p[Z][Q], H.p[Z][P], rho23[Q], rho23[P], G.S[Z], phf,
-                         G.inv_h[Z]) -
+      flux_lo = phit3(D[Q], D[P], H.p[Z][Q], H.p[Z][P], rho23[Q], rho23[P], G.S[Z], phf,
+                      G.inv_h[Z], c.k0 % kf == 0) -
                 w * (pp[P] - pp[Q]);
     }
   }
@@ -1565,20 +1590,20 @@ __global__ __launch_bounds__(64 * TY) void k_correct3(
         const double kd = G.S[d] / G.h[d];
         if (q + 1 < G.n[d]) {
           const double w = 0.5 * (Dc + SD[ho + sd]) * kd;
-          fxy[d] = phit_val(Dc, SD[ho + sd], Hc[d], SH[ho + sd], r23, Sr[ho + sd], G.S[d], phc, G.inv_h[d]) -
+          fxy[d] = phit3(Dc, SD[ho + sd], Hc[d], SH[ho + sd], r23, Sr[ho + sd], G.S[d], phc, G.inv_h[d]) -
                    w * (Sp[ho + sd] - pc);
           sum += fxy[d];
         }
         if (q > 0) {
           const double w = 0.5 * (SD[ho - sd] + Dc) * kd;
-          sum -= phit_val(SD[ho - sd], Dc, SH[ho - sd], Hc[d], Sr[ho - sd], r23, G.S[d], phc, G.inv_h[d]) -
+          sum -= phit3(SD[ho - sd], Dc, SH[ho - sd], Hc[d], Sr[ho - sd], r23, G.S[d], phc, G.inv_h[d]) -
                  w * (pc - Sp[ho - sd]);
         }
       }
       double flux_hi = 0.0;
       if (up) {
         const double w = 0.5 * (Dc + D_up) * kz_;
-        flux_hi = phit_val(Dc, D_up, Hc[Z], Hz_up, r23, r_up, G.S[Z], phi_face<3>(G, ph, Z, k, k),
+        flux_hi = phit3(Dc, D_up, Hc[Z], Hz_up, r23, r_up, G.S[Z], phi_face<3>(G, ph, Z, k, k),
                            G.inv_h[Z]) -
                   w * (p_up - pc);
         sum += flux_hi;
@@ -1748,37 +1773,85 @@ int grid_for(int nc) {
   return need < 1 ? 1 : (need < cap ? need : cap);
 }
 
-// Column tiles of the z-marching kernels: the default chunk of planes, made
-// longer on large meshes so that there are at most kMaxZBlocks workgroups
+// Chunks of at most kc0 planes (the length that measured best where the mesh
+// fills the card) for `cols` columns of tiles: at most kMaxZBlocks workgroups
 // (each leaves per-workgroup partials) unless the columns alone need more.
-template <int NDIM>
-ZPlan zplan_t(const Geo& G) {
-  using T = ZTile<NDIM>;
-  const int ntx = (G.nx + T::TX - 1) / T::TX;
-  const int nty = NDIM == 3 ? (G.ny + T::TY - 1) / T::TY : 1;
-  const int cols = ntx * nty, nz = G.n[NDIM - 1];
-  int kc = T::KC < nz ? T::KC : nz;
-  int nk = (nz + kc - 1) / kc;
+static ZPlan full_plan(int cols, int nz, int kc0) {
+  int kc = kc0 < nz ? kc0 : nz;
   const int maxk = kMaxZBlocks / cols > 1 ? kMaxZBlocks / cols : 1;
-  if (nk > maxk) {
-    kc = (nz + maxk - 1) / maxk;
-    nk = (nz + kc - 1) / kc;
-  }
-  return ZPlan{kc, cols * nk};
+  if ((nz + kc - 1) / kc > maxk) kc = (nz + maxk - 1) / maxk;
+  return ZPlan{kc, cols * ((nz + kc - 1) / kc), kc};
 }
 
-ZPlan zplan(const Geo& G) { return G.ndim == 2 ? zplan_t<2>(G) : zplan_t<3>(G); }
+// Those chunks cut into shorter ones where they would leave CUs idle: a
+// round of `per` workgroups a CU takes about kc + 3 planes' time (the two
+// halo planes and the start-up loads of a chunk), and there are
+// ceil(workgroups / (per CUs)) rounds; a cut has to promise an eighth less,
+// as it re-reads halo planes.  On 64 x 64 x 32 cells (8 workgroups before,
+// 256 now) Step 1 went from 92 to 11.5 us, H from 72 to 7.6, the first
+// correction from 34 to 7, the FP32 / FP64 CG iteration from 42 / 59 to 8.4 /
+// 10 us; on 150 x 90 x 61 cells (36 workgroups before) Step 1 from 188 to 46,
+// H from 133 to 29 us.  A chunk that is cut is cut into equal parts, so
+// every start of a full chunk starts one.
+ZPlan chunk_plan(int cols, int nz, int kc0, int per) {
+  const ZPlan full = full_plan(cols, nz, kc0);
+  const bool one = full.kc >= nz;  // a single chunk may be cut anywhere
+  ZPlan best = full;
+  long least = -1, whole = 0;
+  for (int parts = 1; parts <= full.kc; ++parts) {
+    if (!one && full.kc % parts) continue;
+    const int kc = (full.kc + parts - 1) / parts;
+    const long blocks = (long)cols * ((nz + kc - 1) / kc);
+    if (blocks > kMaxZBlocks && least >= 0) break;
+    const long cost = (blocks + kCus * per - 1) / (kCus * per) * (kc + 3);
+    // (a cut re-reads halo planes: only for a good gain)
+    if (least < 0 || cost < least) {
+      if (least >= 0 && 8 * cost > 7 * whole) continue;
+      if (least < 0) whole = cost;
+      least = cost;
+      best.kc = kc;
+      best.blocks = (int)blocks;
+    }
+  }
+  return best;
+}
+
+// Column tiles of the z-marching kernels.  2D: a wave's tile is 64 columns
+// by kc rows, at most ZTile<2>::KC and short enough for kWaves2 waves (one a
+// SIMD) where the mesh has that many rows: on 200 x 200 cells the explicit
+// kernels went from 11-15 to 4-6 us; shorter ones gained nothing there, and
+// on 1280 x 640 cells 8, 16 and 32 waves a CU were up to 10 % slower than 4.
+ZPlan zplan(const Geo& G) {
+  if (G.ndim == 2) {
+    constexpr long kWaves2 = 4L * kCus;
+    const int ns = (G.nx + 63) / 64, nz = G.n[1], wpb = kBlock / 64;
+    int kc = (int)((long)ns * nz / kWaves2);
+    kc = kc < 1 ? 1 : (kc > ZTile<2>::KC ? ZTile<2>::KC : kc);
+    long nk = (nz + kc - 1) / kc;
+    const long maxk = (long)kMaxZBlocks * wpb / ns > 1 ? (long)kMaxZBlocks * wpb / ns : 1;
+    if (nk > maxk) {
+      kc = (int)((nz + maxk - 1) / maxk);
+      nk = (nz + kc - 1) / kc;
+    }
+    return ZPlan{kc, (int)((ns * nk + wpb - 1) / wpb), kc};
+  }
+  using T = ZTile<3>;
+  const int cols = ((G.nx + T::TX - 1) / T::TX) * ((G.ny + T::TY - 1) / T::TY);
+  return chunk_plan(cols, G.nz, T::KC, 4);
+}
+
+ZPlan zplan_fixed(const Geo& G) {
+  const bool d2 = G.ndim == 2;
+  const int cols = d2 ? (G.nx + kBlock - 1) / kBlock
+                      : ((G.nx + ZTile<3>::TX - 1) / ZTile<3>::TX) * ((G.ny + ZTile<3>::TY - 1) / ZTile<3>::TY);
+  ZPlan zp = full_plan(cols, G.n[G.ndim - 1], d2 ? ZTile<2>::KC : ZTile<3>::KC);
+  if (d2) zp.kc |= kRowSegments;
+  return zp;
+}
 
 ZPlan zplan3(const Geo& G, int ty, int kc0) {
-  const int cols = ((G.nx + 63) / 64) * ((G.ny + ty - 1) / ty), nz = G.nz;
-  int kc = kc0 < nz ? kc0 : nz;
-  int nk = (nz + kc - 1) / kc;
-  const int maxk = kMaxZBlocks / cols > 1 ? kMaxZBlocks / cols : 1;
-  if (nk > maxk) {
-    kc = (nz + maxk - 1) / maxk;
-    nk = (nz + kc - 1) / kc;
-  }
-  return ZPlan{kc, cols * nk};
+  const int cols = ((G.nx + 63) / 64) * ((G.ny + ty - 1) / ty);
+  return chunk_plan(cols, G.nz, kc0, ty >= 8 ? 1 : 2);
 }
 
 namespace {
@@ -1850,11 +1923,11 @@ int launch_energy_rhs(hipStream_t s, const Geo& G, const Phys& ph, bool enth, bo
     return zp.blocks;
   }
   if (enth)
-    hipLaunchKernelGGL((k_energy_rhs3<kTyEnergy, true, true>), dim3(zp3.blocks), dim3(64 * kTyEnergy), 0, s, G, ph, zp3.kc, rho, e0, a_prev, T_prev, V3(phi), rho_star, Ks, Tbg, sy);
+    hipLaunchKernelGGL((k_energy_rhs3<kTyEnergy, true, true>), dim3(zp3.blocks), dim3(64 * kTyEnergy), 0, s, G, ph, zp3.kc, zp3.kf, rho, e0, a_prev, T_prev, V3(phi), rho_star, Ks, Tbg, sy);
   else if (ks)
-    hipLaunchKernelGGL((k_energy_rhs3<kTyEnergy, false, true>), dim3(zp3.blocks), dim3(64 * kTyEnergy), 0, s, G, ph, zp3.kc, rho, e0, a_prev, T_prev, V3(phi), rho_star, Ks, Tbg, sy);
+    hipLaunchKernelGGL((k_energy_rhs3<kTyEnergy, false, true>), dim3(zp3.blocks), dim3(64 * kTyEnergy), 0, s, G, ph, zp3.kc, zp3.kf, rho, e0, a_prev, T_prev, V3(phi), rho_star, Ks, Tbg, sy);
   else
-    hipLaunchKernelGGL((k_energy_rhs3<kTyEnergy, false, false>), dim3(zp3.blocks), dim3(64 * kTyEnergy), 0, s, G, ph, zp3.kc, rho, e0, a_prev, T_prev, V3(phi), rho_star, Ks, Tbg, sy);
+    hipLaunchKernelGGL((k_energy_rhs3<kTyEnergy, false, false>), dim3(zp3.blocks), dim3(64 * kTyEnergy), 0, s, G, ph, zp3.kc, zp3.kf, rho, e0, a_prev, T_prev, V3(phi), rho_star, Ks, Tbg, sy);
   return zp3.blocks;
 }
 
@@ -1921,9 +1994,9 @@ void launch_correct(hipStream_t s, const Geo& G, const Phys& ph, const double* p
   if (G.ndim == 2)
     hipLaunchKernelGGL(k_correct<2>, dim3(zp.blocks), dim3(kBlock), 0, s, G, ph, zp.kc, pp, rho23, psi, V2(H), D, rho_star, V2(u_out), (int)last, rho_old, rho_new, p_new, V2(phi_out), partials);
   else if (last)
-    hipLaunchKernelGGL((k_correct3<true, kTyCorr>), dim3(zp3.blocks), dim3(64 * kTyCorr), 0, s, G, ph, zp3.kc, pp, rho23, psi, V3(H), D, rho_star, V3(u_out), rho_old, rho_new, p_new, V3(phi_out), partials);
+    hipLaunchKernelGGL((k_correct3<true, kTyCorr>), dim3(zp3.blocks), dim3(64 * kTyCorr), 0, s, G, ph, zp3.kc, zp3.kf, pp, rho23, psi, V3(H), D, rho_star, V3(u_out), rho_old, rho_new, p_new, V3(phi_out), partials);
   else
-    hipLaunchKernelGGL((k_correct3<false, kTyCorr>), dim3(zp3.blocks), dim3(64 * kTyCorr), 0, s, G, ph, zp3.kc, pp, rho23, psi, V3(H), D, rho_star, V3(u_out), rho_old, rho_new, p_new, V3(phi_out), partials);
+    hipLaunchKernelGGL((k_correct3<false, kTyCorr>), dim3(zp3.blocks), dim3(64 * kTyCorr), 0, s, G, ph, zp3.kc, zp3.kf, pp, rho23, psi, V3(H), D, rho_star, V3(u_out), rho_old, rho_new, p_new, V3(phi_out), partials);
   if (last)
     hipLaunchKernelGGL(k_finalize_reduce, dim3(1), dim3(kBlock), 0, s, (const double*)partials, zp3.blocks, sc);
 }
