@@ -258,9 +258,10 @@ gea_status gea_get_fields(gea_ctx* ctx, uint32_t field_mask, double* out, gea_pt
  *     that iteration's partials, except at the start of a batch of
  *     iterations; the previous update of r and x, the new direction p,
  *     q = A p, the iteration's partial dot products)
+ *     or, on 2D meshes whose tiles fit the card, the whole solve in one launch
  *   1 FP64 CG scalar kernel (one workgroup, at the end of each batch:
  *     alpha, beta, stop test)
- *   2 FP32 inner CG iteration kernel  3 FP32 inner CG scalar kernel
+ *   2 FP32 inner CG iteration kernel (or whole inner solve)  3 FP32 inner CG scalar kernel
  *   4 solver set-up kernels (initial residual and its scalars, refinement
  *     residual and correction, FP32 coefficient copy)
  *   5 explicit step kernels (Steps 1-3 outside the solve)
@@ -291,11 +292,18 @@ gea_status gea_time_solver_kernels(gea_ctx* ctx, int32_t reps, double* ms);
  * (GEA_ERR_STATE otherwise); overwrites only the network's activations. */
 gea_status gea_time_network(gea_ctx* ctx, int32_t reps, double* ms, double* gflop);
 
+/* Test support: how long (in 10 ns) a workgroup of a one-launch pressure or
+ * energy solve waits for another one before the solve is given up and the
+ * call done again with one launch an iteration; 0: not at all.  (By default
+ * 0.25 s: its workgroups need to be on the card at the same time, which
+ * another program's kernels can prevent.) */
+gea_status gea_set_wait_limit(gea_ctx* ctx, uint64_t ticks);
+
 /* For callers that cannot allocate device memory (work under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the FP64
  * Jacobi-PCG solve of gea_pressure_solve's FP64 form on a system the caller
  * passes, with every work vector, partial sum and solver scalar in one
- * static device array of the library (about 60 MB per GPU, held from the
+ * static device array of the library (about 70 MB per GPU, held from the
  * first call on a device until the process ends).  It allocates nothing
  * and needs no context.
  *   mesh: at most 2^20 cells (GEA_ERR_ARG beyond, see gea_last_error(NULL));

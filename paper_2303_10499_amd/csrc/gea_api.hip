@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -272,6 +273,13 @@ struct gea_ctx {
     if (corr < 8) conv_hist[corr][outer < 3 ? outer : 3] = c;
   }
   std::string err;
+  // one-launch solves: plans of the energy, FP64 and inner FP32 solves
+  // (variant 0 where the mesh takes the iteration kernels) and their exchange area
+  CgpPlan plan_e{}, plan64{}, plan32{};
+  uint64_t* cgx = nullptr;
+  uint64_t spin = kCgpSpin;  // how long a workgroup of theirs waits (gea_set_wait_limit)
+  int dev = 0;
+  std::unique_lock<std::mutex> big;  // see hold_card
   // pinned host buffer the solver scalars are read through (device-to-host
   // copies into it are asynchronous, so several go out with one wait)
   char* pin = nullptr;
@@ -324,6 +332,10 @@ Geo make_geo(const gea_mesh& m) {
 namespace gea {
 Geo mesh_geo(const gea_mesh& m) { return make_geo(m); }
 void set_call_error(const std::string& msg) { g_init_error = msg; }
+std::mutex& card_mutex(int dev) {
+  static std::mutex m[64];
+  return m[dev & 63];
+}
 }  // namespace gea
 
 namespace {
@@ -403,6 +415,7 @@ size_t carve(Carver& cv, gea_ctx* x, const gea_mesh& m, bool learned, bool trans
     w->u[1] = cv.take<double>(2 * (size_t)nzb);
     w->b = cv.take<double>(nzb);
   }
+  x->cgx = cv.take<uint64_t>((size_t)cgp_words(G));
   x->w64.sc = x->sc;
   x->w32.sc = x->sc32;
   x->w64.ns = iter_grid<double>(make_geo(m));
@@ -528,6 +541,7 @@ void read_structs(gea_ctx* x, const Extra* parts, int n) {
     }
   }
   wait_stream(x);
+  if (x->big.owns_lock()) x->big.unlock();  // (no one-launch solve is left on the stream)
   off = 0;
   for (int k = 0; k < n; ++k) {
     std::memcpy(parts[k].host, x->pin + off, parts[k].bytes);
@@ -544,6 +558,21 @@ void read_structs(gea_ctx* x, const Extra* parts, int n) {
 void read_scalars(gea_ctx* x, CgScalars* dev, CgScalars* host, const Extra& extra = Extra{}) {
   const Extra parts[2] = {Extra{dev, host, sizeof(CgScalars)}, extra};
   read_structs(x, parts, extra.bytes ? 2 : 1);
+}
+
+// (see kSharedBlocks) held from here to this context's next read
+void hold_card(gea_ctx* x, const CgpPlan& p) {
+  if (p.blocks > kSharedBlocks && !x->big.owns_lock())
+    x->big = std::unique_lock<std::mutex>(card_mutex(x->dev));
+}
+
+// A one-launch solve gave up waiting: from here on this context takes the
+// iteration kernels, and the call is done again with them.
+struct CgpAborted {};
+void check_cgp(gea_ctx* x, const CgScalars& hs) {
+  if (hs.status != kCgpAborted) return;
+  x->plan_e = x->plan64 = x->plan32 = CgpPlan{};
+  throw CgpAborted{};
 }
 
 // Host loop of one CG solve: enqueue batches of iterations, read the device
@@ -675,10 +704,15 @@ gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
   const CgWork& w = x->w64;
   CgVectors<double> v{xv, x->r, x->r1, x->p0, x->p1, x->q, x->q1, x->c, x->D, x->dinv, x->b};
   x->timer.run(4, x->stream, [&] { cg_init<double>(x->stream, G, v, w, x->prm.tol, x->prm.max_iter); });
+  if (x->plan64.variant) {
+    hold_card(x, x->plan64);
+    x->timer.run(0, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan64, x->cgx, x->spin, x->sc); });
+  }
   HIPCHK(hipGetLastError());
   CgScalars hs;
   read_scalars(x, x->sc, &hs);
-  out->rel_res0 = hs.bb > 0 ? std::sqrt(hs.rr / hs.bb) : 0.0;
+  check_cgp(x, hs);
+  out->rel_res0 = hs.bb > 0 ? std::sqrt(hs.rr0 / hs.bb) : 0.0;
   if (hs.bb == 0.0) {
     HIPCHK(hipMemsetAsync(xv, 0, sizeof(double) * G.nc, x->stream));
     out->iters = 0;
@@ -728,6 +762,22 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     x->timer.run(2, x->stream, [&] { cg_iter_kernel<float>(x->stream, G, v, j, w, fold); });
     if (last || !cg_folds(w)) x->timer.run(3, x->stream, [&] { cg_scalars(x->stream, G, j, w); });
   };
+  // the whole inner solve in one launch, where the mesh has a plan for it
+  const bool one = x->plan32.variant != 0;
+  bool timed = false;
+  auto whole = [&] {
+    timed = x->prm.solver == GEA_LEARNED_MIXED && x->t_iter_ms < 0;
+    hold_card(x, x->plan32);
+    if (timed) HIPCHK(hipEventRecord(x->ev_it[0], x->stream));
+    x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32); });
+    if (timed) HIPCHK(hipEventRecord(x->ev_it[1], x->stream));
+  };
+  auto time_whole = [&](int iters) {  // (after the read that covers it)
+    if (!timed || iters < 2) return;
+    float t = 0.f;
+    HIPCHK(hipEventElapsedTime(&t, x->ev_it[0], x->ev_it[1]));
+    x->t_iter_ms = (double)t / iters;
+  };
   auto last32_of = [&](int o) -> int& {
     return x->last_iters32[x->corr < 8 ? x->corr : 7][o < 3 ? o : 3];
   };
@@ -742,16 +792,22 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     // behind an unread inner solve the check acts only if that solve is done
     residual_check(x, xv, v, budget, true, unread ? x->sc32 : nullptr);
     HIPCHK(hipGetLastError());
-    if (!unread && last32_of(outer) > 0 && x->predict_unconv(outer)) {
+    if (!unread && (one ? !x->predict_conv(outer) : last32_of(outer) > 0 && x->predict_unconv(outer))) {
       // (were this check converged after all, the inner system starts done,
       // its iterate zero, and the correction adds zero)
       snapshot(x, x->sc, &s_res, sizeof s_res);
-      const int n = last32_of(outer);
-      unread_n = n + 4 + n / 32;
-      for (int j = 0; j < unread_n; ++j) iterate(j, j > 0, j == unread_n - 1);
+      if (one) {
+        whole();
+      } else {
+        const int n = last32_of(outer);
+        unread_n = n + 4 + n / 32;
+        for (int j = 0; j < unread_n; ++j) iterate(j, j > 0, j == unread_n - 1);
+      }
       HIPCHK(hipGetLastError());
       snapshot(x, x->sc32, &s_cg, sizeof s_cg);
-      x->timer.run(4, x->stream, [&] { launch_add_correction(x->stream, G, xv, x->d32, x->sc32, x->sc32); });
+      // (a one-launch solve has corrected xv itself)
+      if (!one)
+        x->timer.run(4, x->stream, [&] { launch_add_correction(x->stream, G, xv, x->d32, x->sc32, x->sc32); });
       unread = true;
       unread_outer = outer;
       ++outer;
@@ -764,7 +820,9 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
       unread = false;
       x->note_conv(unread_outer, s_res.done != 0);
       if (out->rel_res0 < 0) out->rel_res0 = s_res.bb > 0 ? std::sqrt(s_res.rr / s_res.bb) : 0.0;
+      check_cgp(x, s_cg);
       total += s_cg.iter;
+      time_whole(s_cg.iter);
       if (s_cg.status == -5) {
         out->status = GEA_ERR_NAN;
         break;
@@ -808,6 +866,13 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     if (total >= x->prm.max_iter) {
       out->status = GEA_ERR_NOCONV;
       break;
+    }
+    if (one) {
+      whole();
+      HIPCHK(hipGetLastError());
+      read_scalars(x, x->sc32, &h32);
+      check_cgp(x, h32);
+      time_whole(h32.iter);
     }
     int& last32 = last32_of(outer);
     const int first = last32 > 0 ? (int)(0.9 * last32) : 0;
@@ -923,6 +988,11 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
     x->timer.run(2, x->stream, [&] { cg_iter_kernel<float>(x->stream, G, v, j, w, fold); });
     if (last || !cg_folds(w)) x->timer.run(3, x->stream, [&] { cg_scalars(x->stream, G, j, w); });
   };
+  const bool one = x->plan32.variant != 0;
+  auto whole = [&] {
+    hold_card(x, x->plan32);
+    x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32); });
+  };
   // network step(s), then Jacobi-PCG resumed from their iterate and residual
   // (when the flexible CG has converged the resumed solve starts done and its
   // iteration kernels return at once); returns the network steps enqueued
@@ -959,12 +1029,16 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
     // correction adds zero.)  The correction and the check are gated on the
     // inner solve being done: when the batch fell short they do nothing, and
     // after the read the same Jacobi-PCG continues where the batch ended.
-    if (use_net && !unread && x->last_iters_res > 0 && x->predict_unconv(outer)) {
+    if (use_net && !unread && (one || x->last_iters_res > 0) && x->predict_unconv(outer)) {
       snapshot(x, x->sc, &s_res, sizeof s_res);
       const int launched = learned_then_resume(budget > 0 ? budget : 1);
       use_net = false;
-      unread_first = x->last_iters_res + 4 + x->last_iters_res / 32;
-      for (int j = 0; j < unread_first; ++j) iterate(j, j > 0, j == unread_first - 1);
+      if (one) {
+        whole();
+      } else {
+        unread_first = x->last_iters_res + 4 + x->last_iters_res / 32;
+        for (int j = 0; j < unread_first; ++j) iterate(j, j > 0, j == unread_first - 1);
+      }
       HIPCHK(hipGetLastError());
       snapshot(x, x->sc32, &s_cg, sizeof s_cg);
       snapshot(x, x->fsc, &s_fcg, sizeof s_fcg);
@@ -982,6 +1056,7 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
       unread_bound = 0;
       x->note_conv(0, s_res.done != 0);
       if (out->rel_res0 < 0) out->rel_res0 = s_res.bb > 0 ? std::sqrt(s_res.rr / s_res.bb) : 0.0;
+      check_cgp(x, s_cg);
       total += s_cg.iter + s_fcg.iter;
       x->last_iters_res = s_cg.iter;
       if (s_fcg.status == 1) ++fallbacks;  // stalled: Jacobi-PCG took over
@@ -1042,6 +1117,20 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
       fcg = Extra{x->fsc, &hf, sizeof hf};
       first = x->last_iters_res > 0 ? x->last_iters_res + 4 : 0;
     }
+    if (one) {
+      const bool timed = x->t_iter_ms < 0;
+      if (timed) HIPCHK(hipEventRecord(x->ev_it[0], x->stream));
+      whole();
+      if (timed) HIPCHK(hipEventRecord(x->ev_it[1], x->stream));
+      HIPCHK(hipGetLastError());
+      read_scalars(x, x->sc32, &h32, fcg);
+      check_cgp(x, h32);
+      if (timed && h32.iter >= 2) {
+        float t = 0.f;
+        HIPCHK(hipEventElapsedTime(&t, x->ev_it[0], x->ev_it[1]));
+        x->t_iter_ms = (double)t / h32.iter;
+      }
+    }
     gea_status rc = run_cg(x, x->sc32, h32, budget, first, iterate, fcg, 0, true);
     if (rc != GEA_OK) return rc;
     done_iters += h32.iter;
@@ -1088,6 +1177,13 @@ gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters
     cg_start_from(x->stream, w.u[1], nparts, w.b, kEnergyTol, x->prm.max_iter, w.sc);
   });
   CgScalars hs{};  // rr = 0: the first read supplies the starting residual
+  if (x->plan_e.variant) {
+    hold_card(x, x->plan_e);
+    x->timer.run(7, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan_e, x->cgx, x->spin, w.sc); });
+    read_scalars(x, x->sc, &hs);
+    check_cgp(x, hs);
+    if (!hs.done) hs = CgScalars{};  // (b = 0)
+  }
   int& last = x->last_iters_energy[sweep < 8 ? sweep : 7];
   gea_status rc = run_cg(
       x, x->sc, hs, x->prm.max_iter, last > 0 ? last + 1 : 0,
@@ -1351,8 +1447,21 @@ hipMemcpyKind kind_out(gea_ptr_kind k) {
 
 template <typename F>
 gea_status guarded(gea_ctx* x, F&& f) {
+  struct Release {  // (an error may leave with the card held)
+    gea_ctx* x;
+    ~Release() {
+      if (x->big.owns_lock()) x->big.unlock();
+    }
+  } release{x};
   try {
-    return f();
+    try {
+      return f();
+    } catch (const CgpAborted&) {
+      x->tail = nullptr;
+      x->nsnap = 0;
+      x->res_parts = 0;
+      return f();  // (the calls that solve change no state before their solves end well)
+    }
   } catch (const HipError& e) {
     char buf[256];
     std::snprintf(buf, sizeof buf, "HIP error %d (%s) in %s", (int)e.e, hipGetErrorString(e.e),
@@ -1425,6 +1534,12 @@ gea_status gea_init_mesh(const gea_mesh* mesh, const gea_params* params, void* h
     // zero the solver scalars once
     HIPCHK(hipMemsetAsync(x->sc, 0, sizeof(CgScalars), x->stream));
     HIPCHK(hipMemsetAsync(x->sc32, 0, sizeof(CgScalars), x->stream));
+    if (const size_t words = (size_t)cgp_words(x->G))
+      HIPCHK(hipMemsetAsync(x->cgx, 0, sizeof(uint64_t) * words, x->stream));
+    HIPCHK(hipGetDevice(&x->dev));
+    x->plan_e = cgp_plan<double>(x->G, true);
+    x->plan64 = cgp_plan<double>(x->G, false);
+    x->plan32 = cgp_plan<float>(x->G, false);
     HIPCHK(hipGetLastError());
     for (hipEvent_t* e : {&x->ev_net[0], &x->ev_net[1], &x->ev_it[0], &x->ev_it[1]})
       HIPCHK(hipEventCreate(e));
@@ -1542,7 +1657,7 @@ gea_status gea_step(gea_ctx* x, int32_t nsteps, gea_step_stats* stats) {
   gea_step_stats* st = stats ? stats : &local;
   *st = gea_step_stats{};
   return guarded(x, [&]() {
-    for (int n = 0; n < nsteps; ++n) {
+    for (int n = st->steps_done; n < nsteps; ++n) {
       gea_status rc = one_step(x, st);
       if (rc != GEA_OK) {
         HIPCHK(hipStreamSynchronize(x->stream));
@@ -1755,6 +1870,12 @@ gea_status gea_kernel_times(gea_ctx* x, double* ms, int64_t* launches) {
   });
 }
 
+gea_status gea_set_wait_limit(gea_ctx* x, uint64_t ticks) {
+  if (!x) return GEA_ERR_ARG;
+  x->spin = ticks;
+  return GEA_OK;
+}
+
 gea_status gea_load_weights(gea_ctx* x, const float* params, gea_ptr_kind kind) {
   if (!x) return GEA_ERR_ARG;
   if (!params) return fail(x, GEA_ERR_ARG, "null params");
@@ -1795,12 +1916,18 @@ gea_status gea_make_pair(gea_ctx* x, double rel_tol, float* in_r, float* in_a, f
     const size_t n = sizeof(double) * G.nc;
     HIPCHK(hipMemcpyAsync(x->xs, S.pp, n, hipMemcpyDeviceToDevice, s));
     launch_sub(s, G, x->b, x->r64);
-    gea_params keep = x->prm;
-    x->prm.tol = rel_tol;
-    x->prm.max_iter = 200000;
+    struct Keep {  // (also when the solve throws)
+      gea_ctx* x;
+      gea_params prm;
+      ~Keep() { x->prm = prm; }
+    };
     gea_solve_stats st;
-    gea_status rc = solve_pcg64(x, x->xs, &st);
-    x->prm = keep;
+    const gea_status rc = [&] {
+      const Keep keep{x, x->prm};
+      x->prm.tol = rel_tol;
+      x->prm.max_iter = 200000;
+      return solve_pcg64(x, x->xs, &st);
+    }();
     if (rc != GEA_OK) return fail(x, rc, "pair solve failed");
     float* tr = in_r;
     float* ta = in_a;

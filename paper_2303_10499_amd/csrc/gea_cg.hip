@@ -124,37 +124,14 @@ __device__ __forceinline__ double* iter_part(double* part, int ns, int iter) {
   return part + (iter & 1) * 7L * ns;
 }
 
-// alpha, the residual after the update, beta and the stop test of iteration
-// `iter` from its ns partials (see the file header); every thread of every
+// the scalars of iteration `iter` from its ns partials; every thread of every
 // workgroup that forms them gets the same values
-struct StepScalars {
-  double alpha, beta, rz, rr;
-  int fin, status;
-  bool bad;
-};
 __device__ __forceinline__ StepScalars step_scalars(const double* part, int ns, int iter,
                                                     const CgScalars* sc) {
   double s[7];
   // (few registers, and the iteration kernels' first loads stay in flight)
   sum_partials<7, 2, true>(part, ns, s);
-  const double pq = s[0], qz = s[1], qmq = s[2], rr0 = s[3], qr = s[4], qq = s[5], rz0 = s[6];
-  StepScalars o;
-  o.alpha = rz0 / pq;
-  o.rz = rz0 - 2.0 * o.alpha * qz + o.alpha * o.alpha * qmq;
-  o.rr = fmax(rr0 - 2.0 * o.alpha * qr + o.alpha * o.alpha * qq, 0.0);
-  o.beta = o.rz / rz0;
-  o.bad = !isfinite(o.alpha) || !isfinite(o.rz) || !isfinite(o.rr) || !isfinite(o.beta);
-  o.fin = 0;
-  o.status = 0;
-  if (o.bad) {
-    o.status = -5;
-  } else if (o.rr <= sc->tol2 * sc->bb) {
-    o.fin = 1;
-  } else if (iter + 1 >= sc->max_iter) {
-    o.fin = 1;
-    o.status = -4;
-  }
-  return o;
+  return scalars_of(s, iter, sc->tol2 * sc->bb, sc->max_iter);
 }
 
 // (one thread) the scalars of iteration `iter` for the host and the next

@@ -243,6 +243,47 @@ void cg_iter_kernel(hipStream_t s, const Geo& G, const CgVectors<T>& v, int iter
                     bool fold);
 void cg_scalars(hipStream_t s, const Geo& G, int iter, const CgWork& w);
 bool cg_folds(const CgWork& w);
+// ---- one-launch solves (gea_cgp.hip) -----------------------------------------
+// A whole solve set up as for cg_iter_kernel (residual in v.r, initial x,
+// scalars in sc) in one launch, for 2D meshes whose workgroups fit the card
+// at once (plan.variant 0: they do not).  It leaves the scalars as the
+// iteration kernels do (done, iter, rr, status, corrected); a system with
+// ||b|| = 0 or done already is left alone.
+constexpr int kCgpAborted = -100;           // status: a wait for another workgroup outlasted kCgpSpin
+constexpr uint64_t kCgpSpin = 25000000ull;  // 0.25 s of the 100 MHz clock
+// Two one-launch solves of two streams that each hold part of the card and
+// wait for the rest of their workgroups would both run into that limit: a
+// launch of more workgroups than this holds the card's mutex from its
+// enqueueing to the host's read of its end.  (Smaller ones fit beside each
+// other: a process has four hardware queues.)
+constexpr int kSharedBlocks = 48;
+struct CgpPlan {
+  int variant;  // 1 + index of the kernel, 0: none
+  int wx, nbx, blocks;
+  long words;   // 64-bit words of the exchange area, zero before its first launch
+};
+template <typename T>
+struct CgSolve {
+  T* x;
+  const T* r;
+  const T* c;
+  const T* D;
+  const T* dinv;
+  T Dc;
+  double* xo;
+};
+struct CgpGrid {
+  uint64_t* ex;   // the exchange area; word 0: the last tag used
+  uint64_t spin;
+  int wx, nbx;
+};
+template <typename T>
+CgpPlan cgp_plan(const Geo& G, bool cd);
+long cgp_words(const Geo& G);  // the most that a plan on the mesh needs, on any device
+template <typename T>
+void cgp_solve(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgpPlan& p, uint64_t* ex,
+               uint64_t spin, CgScalars* sc);  // spin: limit of a wait (0: none is waited)
+
 // Jacobi-PCG resumed on the FP32 inner system from its current iterate and
 // residual, keeping the set-up's ||b||^2 and tolerance: its scalars from
 // 2 x n partials <r, r/diag>, <r, r> of that residual (fcg_handover forms

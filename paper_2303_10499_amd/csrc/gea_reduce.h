@@ -263,6 +263,37 @@ __device__ __forceinline__ Stage3<HW, TY> stage3(const Geo& G, const Col& c) {
 // coordinate of the column along an x/y direction
 __device__ __forceinline__ int coord(const Col& c, int d) { return d == 0 ? c.i : c.j; }
 
+// alpha, the residual after the update, beta and the stop test of a CG
+// iteration from its seven sums <p,q>, <q,z>, <q,q/diag>, <r,r>, <q,r>, <q,q>,
+// <r,z> (see gea_cg.hip)
+struct StepScalars {
+  double alpha, beta, rz, rr;
+  int fin, status;
+  bool bad;
+};
+__device__ __forceinline__ StepScalars scalars_of(const double (&s)[7], int iter, double tolbb,
+                                                  int max_iter) {
+  const double pq = s[0], qz = s[1], qmq = s[2], rr0 = s[3], qr = s[4], qq = s[5], rz0 = s[6];
+  StepScalars o;
+  o.alpha = rz0 / pq;
+  const double a2 = 2.0 * o.alpha, aa = o.alpha * o.alpha;
+  o.rz = __builtin_fma(aa, qmq, __builtin_fma(-a2, qz, rz0));
+  o.rr = fmax(__builtin_fma(aa, qq, __builtin_fma(-a2, qr, rr0)), 0.0);
+  o.beta = o.rz / rz0;
+  o.bad = !isfinite(o.alpha) || !isfinite(o.rz) || !isfinite(o.rr) || !isfinite(o.beta);
+  o.fin = 0;
+  o.status = 0;
+  if (o.bad) {
+    o.status = -5;
+  } else if (o.rr <= tolbb) {
+    o.fin = 1;
+  } else if (iter + 1 >= max_iter) {
+    o.fin = 1;
+    o.status = -4;
+  }
+  return o;
+}
+
 template <int NDIM, typename T>
 struct Stencil {
   T k[NDIM];  // S_d / h_d in the working precision

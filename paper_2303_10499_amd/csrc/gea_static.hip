@@ -19,6 +19,7 @@ namespace gea {
 // defined in gea_api.hip
 Geo mesh_geo(const gea_mesh& m);
 void set_call_error(const std::string& msg);
+std::mutex& card_mutex(int dev);
 
 namespace {
 
@@ -28,8 +29,9 @@ constexpr int kStaticVectors = 7;             // r, r1, p0, p1, q, q1, 1/diag
 constexpr long kStaticIterParts = 7L * 65536;  // 7 partials per iteration-kernel workgroup, two parity sets
 constexpr long kStaticSetupParts = 3L * kMaxZBlocks;  // set-up: 2 + 1 per workgroup
 constexpr long kStaticScalarDoubles = 32;     // one CgScalars (256 bytes)
-constexpr long kStaticDoubles =
-    kStaticVectors * kStaticMaxCells + kStaticIterParts + kStaticSetupParts + kStaticScalarDoubles;
+constexpr long kStaticExchange = 1228800;     // words of the one-launch solve's exchange area
+constexpr long kStaticDoubles = kStaticVectors * kStaticMaxCells + kStaticIterParts +
+                                kStaticSetupParts + kStaticScalarDoubles + kStaticExchange;
 static_assert(sizeof(CgScalars) <= kStaticScalarDoubles * sizeof(double), "scalar slot");
 
 }  // namespace
@@ -165,6 +167,18 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
                      (long)(sizeof(CgScalars) / sizeof(double)), reinterpret_cast<double*>(sc), 0.0);
   hipLaunchKernelGGL(k_static_diag_inv, dim3(grid_for(G.nc)), dim3(kBlock), 0, s, G, c, D, vec[6]);
   cg_init<double>(s, G, v, w, tol, max_iter);
+  // the whole solve in one launch where the mesh has a plan for it (its
+  // exchange area: zero from the start, its words tagged from launch to launch)
+  const CgpPlan plan = cgp_plan<double>(G, false);
+  uint64_t* const ex = reinterpret_cast<uint64_t*>(sc) + kStaticScalarDoubles;
+  const bool one = plan.variant && plan.words <= kStaticExchange;
+  int dev = 0;
+  if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e, "hipGetDevice");
+  std::unique_lock<std::mutex> alone(card_mutex(dev), std::defer_lock);
+  if (one) {
+    if (plan.blocks > kSharedBlocks) alone.lock();
+    cgp_solve<double>(s, G, v, plan, ex, kCgpSpin, sc);
+  }
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve set-up");
   CgScalars hs;
   auto read = [&]() -> hipError_t {
@@ -172,7 +186,17 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
     return r != hipSuccess ? r : hipStreamSynchronize(s);
   };
   if ((e = read()) != hipSuccess) return hip_fail(e, "reading the solver scalars");
-  stats->rel_res0 = hs.bb > 0 ? std::sqrt(hs.rr / hs.bb) : 0.0;
+  if (hs.status == kCgpAborted) {
+    // its workgroups were not on the card together: clear the area and solve
+    // with the iteration kernels from the x it left
+    hipLaunchKernelGGL(k_static_fill, dim3(grid_for((int)kStaticExchange)), dim3(kBlock), 0, s,
+                       kStaticExchange, reinterpret_cast<double*>(ex), 0.0);
+    cg_init<double>(s, G, v, w, tol, max_iter);
+    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve set-up");
+    if ((e = read()) != hipSuccess) return hip_fail(e, "reading the solver scalars");
+  }
+  if (alone.owns_lock()) alone.unlock();
+  stats->rel_res0 = hs.bb > 0 ? std::sqrt(hs.rr0 / hs.bb) : 0.0;
   if (hs.bb == 0.0) {  // b = 0: x = 0
     hipLaunchKernelGGL(k_static_fill, dim3(grid_for(G.nc)), dim3(kBlock), 0, s, (long)G.nc, x, 0.0);
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_fail(e, "clearing x");

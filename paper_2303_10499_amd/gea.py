@@ -100,6 +100,7 @@ def lib():
         L.gea_kernel_times.argtypes = [vp, P(C.c_double), P(C.c_int64)]
         L.gea_time_solver_kernels.argtypes = [vp, C.c_int32, P(C.c_double)]
         L.gea_time_network.argtypes = [vp, C.c_int32, P(C.c_double), P(C.c_double)]
+        L.gea_set_wait_limit.argtypes = [vp, C.c_uint64]
         L.gea_state_extrema.argtypes = [vp, P(Extrema)]
         L.gea_pressure_solve_static.argtypes = [P(Mesh), dp, dp, dp, dp, C.c_double, C.c_int32,
                                                 vp, P(SolveStats)]
@@ -112,7 +113,7 @@ def lib():
                      "gea_apply_pressure_operator", "gea_get_fields", "gea_kernel_timing",
                      "gea_kernel_times", "gea_time_solver_kernels", "gea_time_network",
                      "gea_pressure_solve_static", "gea_state_extrema", "gea_set_face_flux",
-                     "gea_set_history"):
+                     "gea_set_history", "gea_set_wait_limit"):
             getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
