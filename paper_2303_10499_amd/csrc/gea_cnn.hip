@@ -33,7 +33,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMT = 2;  // 16-cell M tiles per wave in the convolution
-constexpr int kPixPerSplit = 512;
 
 __device__ __forceinline__ bf16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -439,7 +438,7 @@ __global__ __launch_bounds__(256) void k_conv0(CnnDims d, const uint32_t* __rest
 // multiply-adds per cell, no padded output channels.
 template <int NDIM>
 struct Conv5Z {
-  static constexpr int TX = NDIM == 3 ? 64 : 256, TY = NDIM == 3 ? 4 : 1, KC = 16;
+  static constexpr int TX = NDIM == 3 ? 64 : 256, TY = NDIM == 3 ? 4 : 1;
   static constexpr int HX = TX + 2, HY = NDIM == 3 ? TY + 2 : 1;
   static constexpr int HC = HX * HY;                // staged cells per plane
   static constexpr int NL = (2 * HC + 255) / 256;   // 16-byte loads per thread and plane
@@ -459,7 +458,7 @@ __device__ __forceinline__ float dot16(const uint4& p, const uint4& q, const uin
 // With scale given, Y receives (float)*scale times the output (the solver's
 // scaled correction; the same product as the output scaling kernel).
 template <int NDIM>
-__global__ __launch_bounds__(256) void k_conv5z(CnnDims d, const bf16_t* __restrict__ X,
+__global__ __launch_bounds__(256) void k_conv5z(CnnDims d, int kc, const bf16_t* __restrict__ X,
                                                 const uint32_t* __restrict__ W5,
                                                 const float* __restrict__ bias,
                                                 float* __restrict__ Y,
@@ -471,8 +470,8 @@ __global__ __launch_bounds__(256) void k_conv5z(CnnDims d, const bf16_t* __restr
   const int b = xcd_block();
   const int ox = (b % ntx) * T::TX;
   const int oy = NDIM == 3 ? ((b / ntx) % nty) * T::TY : 0;
-  const int k0 = (b / (ntx * nty)) * T::KC;
-  const int k1 = min(k0 + T::KC, d.nz);
+  const int k0 = (b / (ntx * nty)) * kc;
+  const int k1 = min(k0 + kc, d.nz);
   const int lx = (int)threadIdx.x % T::TX, ly = (int)threadIdx.x / T::TX;
   const int gx = ox + lx, gy = oy + ly;
   const bool act = gx < d.nx && gy < d.ny;
@@ -549,11 +548,31 @@ __global__ __launch_bounds__(256) void k_conv5z(CnnDims d, const bf16_t* __restr
   }
 }
 
-template <int NDIM>
-int conv5z_tiles(const CnnDims& d) {
-  using T = Conv5Z<NDIM>;
-  return ((d.nx + T::TX - 1) / T::TX) * (NDIM == 3 ? (d.ny + T::TY - 1) / T::TY : 1) *
-         ((d.nz + T::KC - 1) / T::KC);
+// Planes per workgroup of the z-marching convolutions, at most kc0 (what a
+// grid that fills the card takes) and less where that would leave CUs idle:
+// a workgroup's time is about kc + 3 planes (the two halo planes, the weights
+// and the start-up loads), in rounds of `per` workgroups a CU.  Multiples of
+// `unit` planes (the pooling layer takes z pairs).  An output plane's sum does
+// not depend on it.  On 32^3 cells, where kc0 planes gave 2 to 16 workgroups,
+// layer 3 went from 98 to 21 us, layer 4 from 89 to 14, layer 0 from 40 to 8,
+// layer 5 from 35 to 9.
+struct ConvPlan {
+  int kc, blocks;
+};
+ConvPlan conv_plan(const CnnDims& d, int tx, int ty, int kc0, int per, int unit = 1) {
+  const long cols = (long)((d.nx + tx - 1) / tx) * ((d.ny + ty - 1) / ty);
+  ConvPlan best{kc0, 0};
+  long least = 0;
+  for (int kc = kc0; kc >= unit; kc -= unit) {
+    const long wg = cols * ((d.nz + kc - 1) / kc);
+    const long cost = (wg + kCus * per - 1) / (kCus * per) * ((kc < d.nz ? kc : d.nz) + 3);
+    if (kc == kc0 || 8 * cost < 7 * least) {
+      least = cost;
+      best.kc = kc;
+    }
+  }
+  best.blocks = (int)(cols * ((d.nz + best.kc - 1) / best.kc));
+  return best;
 }
 
 template <int NDIM, int CIN>
@@ -565,88 +584,208 @@ int conv_tiles(const CnnDims& d) {
   return ntx * nty * ntz;
 }
 
-// Weight gradient partials: part[split][co][n] = sum over the split's cells
-// p of dY[p][co] * X[p + off(tap(n))][ci(n)], n = tap*CIN + ci.
+// Weight gradient: dW[co][tap][ci] = sum over the cells p of
+// dY[p][co] X[p + tap][ci], a contraction over cells.  A workgroup owns one
+// 16-channel tile of the inputs (blockIdx.x) and a run of cell tiles (one
+// split, blockIdx.y) of 8 x-cells by 32 rows (3D: 8 y x 4 z), and each wave a
+// quarter of the taps with all output channels.  A tile of X with its halo and
+// the tile of dY are copied to LDS as they lie in memory, [cell][channel];
+// both operands need eight cells of one channel per lane, which the
+// transposing LDS read gives, and a tap is only an offset of its address.
+// FP32 accumulators over the split, one partial per split; the bias gradient
+// sums the dY tile that is there already.  On 32^3 cells the latency of one
+// tile's load and of its eight chunks bounds it: 10-14 us a layer, where
+// gathering every operand element by element from global memory took 36-85
+// (and a pass of its own over dY for the bias 20).
+template <int NDIM>
+struct WgradTile {
+  static constexpr int TX = 8, TY = NDIM == 3 ? 8 : 1, TZ = NDIM == 3 ? 4 : 32;
+  static constexpr int HX = TX + 2, HY = NDIM == 3 ? TY + 2 : 1, HZ = TZ + 2;
+  static constexpr int SX = 12;  // row stride in LDS (cells): four rows of a chunk in distinct banks by pairs
+  static constexpr int CELLS = TX * TY * TZ, CHUNKS = CELLS / 32;
+  static constexpr int XU = HX * HY * HZ;                  // staged cells
+  static constexpr int XB = SX * HY * HZ * 32;             // bytes of them
+};
+
+// Splits of the cells: as many as give three workgroups a CU over the input
+// channel tiles, at most one per cell tile.
+struct WgradPlan {
+  int tiles, per, nsplit;  // cell tiles, tiles per split, splits
+};
+WgradPlan wgrad_plan(const CnnDims& d, int ndim, int cin_p) {
+  const int tx = (d.nx + 7) / 8;
+  const int tyz = ndim == 3 ? ((d.ny + 7) / 8) * ((d.nz + 3) / 4) : (d.nz + 31) / 32;
+  WgradPlan w;
+  w.tiles = tx * tyz;
+  const int want = 3 * kCus / ((cin_p + 15) / 16);
+  const int n = w.tiles < want ? w.tiles : want;
+  w.per = (w.tiles + n - 1) / n;
+  w.nsplit = (w.tiles + w.per - 1) / w.per;
+  return w;
+}
+
+// eight cells of this lane's channel, as an MFMA operand: two transposing
+// reads of four cells each.  In a group of 16 lanes, lane l names four
+// channels (8 bytes) of cell l / 4 and receives channel l of the four cells.
+__device__ __forceinline__ uint4 cells8(const unsigned char* lo, int stride4) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lptr;
+  const s16x4 u = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(lo));
+  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lptr)(lo + stride4));
+  const uint2 a = __builtin_bit_cast(uint2, u), b = __builtin_bit_cast(uint2, v);
+  return make_uint4(a.x, a.y, b.x, b.y);
+}
+
 template <int NDIM, int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_wgrad(CnnDims d, const bf16_t* __restrict__ X,
+__global__ __launch_bounds__(256) void k_wgrad(CnnDims d, WgradPlan w, const bf16_t* __restrict__ X,
                                                const bf16_t* __restrict__ dY,
-                                               float* __restrict__ part) {
+                                               float* __restrict__ part, double* __restrict__ bpart) {
+  using T = WgradTile<NDIM>;
   constexpr int NT = Taps<NDIM>::n;
   constexpr int KPAD = (NT * CIN + 31) / 32 * 32;
   constexpr int MTI = COUT / 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int TW = (NT + 3) / 4;             // taps per wave
+  constexpr int XH = CIN < 16 ? 1 : 2;         // 16-byte units per staged cell
+  constexpr int DU = T::CELLS * COUT / 8;      // 16-byte units of the dY tile
+  __shared__ __attribute__((aligned(16))) unsigned char sX[T::XB];
+  __shared__ __attribute__((aligned(16))) unsigned char sD[T::CELLS * COUT * 2];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r = lane & 15;
-  const int n0 = (blockIdx.x * 4 + wave) * 16;
-  if (n0 >= KPAD) return;  // no workgroup barrier below
+  const int ci0 = blockIdx.x * 16;
   const int split = blockIdx.y;
-  const int p_beg = split * kPixPerSplit;
-  const int p_end = min(p_beg + kPixPerSplit, d.npix);
-  const int n = n0 + r;
-  const int t = n / CIN, ci = n % CIN;
-  f32x4 acc[MTI];
+  const int ntx = (d.nx + T::TX - 1) / T::TX;
+  const int nty = NDIM == 3 ? (d.ny + T::TY - 1) / T::TY : 1;
+  f32x4 acc[TW][MTI];
 #pragma unroll
-  for (int mt = 0; mt < MTI; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int p0 = p_beg; p0 < p_end; p0 += 32) {
-    bf16x8 b;
+  for (int u = 0; u < TW; ++u)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int p = p0 + 8 * g + i;
-      bf16_t v = 0;
-      if (p < p_end && t < NT) {
-        int a, bb, c;
-        coords<NDIM>(d, p, a, bb, c);
-        const int q = neighbor<NDIM>(d, a, bb, c, t);
-        if (q >= 0) v = X[(size_t)q * CIN + ci];
-      }
-      b[i] = __builtin_bit_cast(__bf16, v);
+    for (int mt = 0; mt < MTI; ++mt) acc[u][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // this lane's reads: row g of a chunk, cell r / 4, channels 4 (r % 4) ...
+  const unsigned char* xa = sX + (g * T::SX + (r >> 2)) * 32 + (r & 3) * 8;
+  const unsigned char* da = sD + (g * T::TX + (r >> 2)) * (COUT * 2) + (r & 3) * 8;
+  int toff[TW];  // byte offset of each tap, wave-uniform
+#pragma unroll
+  for (int u = 0; u < TW; ++u) {
+    const int t = min(wave * TW + u, NT - 1);
+    toff[u] = NDIM == 3 ? ((t / 9 * T::HY + (t / 3) % 3) * T::SX + t % 3) * 32
+                        : (t / 3 * T::SX + t % 3) * 32;
+  }
+  if (XH == 1)  // 8 padded input channels: the upper half of a staged cell stays 0
+    for (int e = threadIdx.x; e < T::XB / 16; e += 256)
+      *reinterpret_cast<uint4*>(sX + e * 16) = make_uint4(0, 0, 0, 0);
+  double bsum = 0.0;
+  const int t0 = split * w.per, t1 = min(t0 + w.per, w.tiles);
+  for (int tile = t0; tile < t1; ++tile) {
+    const int x0 = (tile % ntx) * T::TX, y0 = NDIM == 3 ? ((tile / ntx) % nty) * T::TY : 0;
+    const int z0 = (tile / (ntx * nty)) * T::TZ;
+    __syncthreads();  // the tile before has been read
+    // every load is made, from an index clamped into the grid; zeros outside
+#pragma unroll
+    for (int e0 = 0; e0 < T::XU * XH; e0 += 256) {
+      const int e = e0 + threadIdx.x;
+      const int c = min(e / XH, T::XU - 1), h = e % XH;
+      const int lx = c % T::HX, lr = c / T::HX;
+      const int x = x0 + lx - 1, y = NDIM == 3 ? y0 + lr % T::HY - 1 : 0, z = z0 + lr / T::HY - 1;
+      const bool in = x >= 0 && x < d.nx && y >= 0 && y < d.ny && z >= 0 && z < d.nz;
+      const int xc = min(max(x, 0), d.nx - 1), yc = min(max(y, 0), d.ny - 1), zc = min(max(z, 0), d.nz - 1);
+      const uint4 v = *reinterpret_cast<const uint4*>(X + (xc + (size_t)d.nx * (yc + (size_t)d.ny * zc)) * CIN + ci0 + 8 * h);
+      if (e < T::XU * XH)
+        *reinterpret_cast<uint4*>(sX + (lr * T::SX + lx) * 32 + h * 16) = in ? v : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
-    for (int mt = 0; mt < MTI; ++mt) {
-      bf16x8 a;
+    for (int e0 = 0; e0 < DU; e0 += 256) {
+      const int e = e0 + threadIdx.x, c = e / (COUT / 8), h = e % (COUT / 8);
+      const int x = x0 + c % T::TX, y = NDIM == 3 ? y0 + (c / T::TX) % T::TY : 0, z = z0 + c / (T::TX * T::TY);
+      const bool in = x < d.nx && y < d.ny && z < d.nz;
+      const int xc = min(x, d.nx - 1), yc = min(y, d.ny - 1), zc = min(z, d.nz - 1);
+      const uint4 v = *reinterpret_cast<const uint4*>(dY + (xc + (size_t)d.nx * (yc + (size_t)d.ny * zc)) * COUT + 8 * h);
+      *reinterpret_cast<uint4*>(sD + e * 16) = in ? v : make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    const bool over = x0 + T::TX > d.nx || (NDIM == 3 && y0 + T::TY > d.ny) || z0 + T::TZ > d.nz;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int p = p0 + 8 * g + i;
-        const bf16_t v = p < p_end ? dY[(size_t)p * COUT + mt * 16 + r] : (bf16_t)0;
-        a[i] = __builtin_bit_cast(__bf16, v);
+    for (int c = 0; c < T::CHUNKS; ++c) {
+      // chunk c: rows 4c ... 4c + 3 of the tile (3D: half the y rows of plane c / 2)
+      const int row = NDIM == 3 ? (c / 2 * T::HY + c % 2 * 4) * T::SX : c * 4 * T::SX;
+      bf16x8 a[MTI];
+#pragma unroll
+      for (int mt = 0; mt < MTI; ++mt)
+        a[mt] = __builtin_bit_cast(bf16x8, cells8(da + c * 32 * COUT * 2 + mt * 32, 4 * COUT * 2));
+      uint32_t mk[4];
+      if (over) {  // cells outside the grid take no part, whatever X holds beside them
+        const bool rin = NDIM == 3 ? y0 + c % 2 * 4 + g < d.ny && z0 + c / 2 < d.nz : z0 + c * 4 + g < d.nz;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          mk[i] = (rin && x0 + 2 * i < d.nx ? 0xFFFFu : 0u) | (rin && x0 + 2 * i + 1 < d.nx ? 0xFFFF0000u : 0u);
       }
-      acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[mt], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < TW; ++u) {
+        uint4 b = cells8(xa + toff[u] + row * 32, 4 * 32);
+        if (over) b = make_uint4(b.x & mk[0], b.y & mk[1], b.z & mk[2], b.w & mk[3]);
+#pragma unroll
+        for (int mt = 0; mt < MTI; ++mt)
+          acc[u][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], __builtin_bit_cast(bf16x8, b), acc[u][mt], 0, 0, 0);
+      }
+    }
+    if (blockIdx.x == 0) {  // the bias gradient's share, in FP64: thread = (cell group, channel)
+      const bf16_t* sd = reinterpret_cast<const bf16_t*>(sD);
+#pragma unroll 8
+      for (int q = threadIdx.x / COUT; q < T::CELLS; q += 256 / COUT)
+        bsum += (double)bf2f(sd[q * COUT + threadIdx.x % COUT]);
     }
   }
 #pragma unroll
-  for (int mt = 0; mt < MTI; ++mt)
+  for (int u = 0; u < TW; ++u) {
+    const int t = wave * TW + u;
+    if (t >= NT || r >= CIN) continue;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int co = mt * 16 + 4 * g + i;
-      part[((size_t)split * COUT + co) * KPAD + n0 + r] = acc[mt][i];
+    for (int mt = 0; mt < MTI; ++mt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        part[((size_t)split * COUT + mt * 16 + 4 * g + i) * KPAD + t * CIN + ci0 + r] = acc[u][mt][i];
+  }
+  if (blockIdx.x == 0) {
+    double* sb = reinterpret_cast<double*>(sX);
+    __syncthreads();
+    sb[threadIdx.x] = bsum;
+    __syncthreads();
+    if (threadIdx.x < COUT) {
+      double s = 0.0;
+      for (int q = 0; q < 256 / COUT; ++q) s += sb[q * COUT + threadIdx.x];
+      bpart[(size_t)split * COUT + threadIdx.x] = s;
     }
+  }
 }
 
-// Sum the weight-gradient partials in split order into the packed gradient
-// (logical layout W[co][tap][ci]); the bias gradient sums dY over the cells.
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int nsplit,
+// Sum the weight- and bias-gradient partials over the splits into the packed
+// gradient (logical layout W[co][tap][ci], then b[co]), in FP64: 16 threads
+// share an element, so that few elements over many splits fill the chip too
+// (4-6 us a layer on 32^3 cells; one thread an element took 16).
+__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part,
+                                                      const double* __restrict__ bpart, int nsplit,
                                                       int cout_p, int kpad, int cin, int cin_p,
                                                       int cout, int ntaps, float* __restrict__ gW,
                                                       int accumulate) {
-  const int total = cout * ntaps * cin;
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < total; e += gridDim.x * blockDim.x) {
+  __shared__ double sh[16][17];
+  const int nW = cout * ntaps * cin, total = nW + cout;
+  const int le = threadIdx.x & 15, ls = threadIdx.x >> 4;
+  const int e = blockIdx.x * 16 + le;
+  double s = 0.0;
+  if (e < nW) {
     const int ci = e % cin, t = (e / cin) % ntaps, co = e / (cin * ntaps);
-    const int n = t * cin_p + ci;
-    float s = 0.f;
-    for (int sp = 0; sp < nsplit; ++sp) s += part[((size_t)sp * cout_p + co) * kpad + n];
-    gW[e] = accumulate ? gW[e] + s : s;
+    const float* p = part + (size_t)co * kpad + t * cin_p + ci;
+    const size_t st = (size_t)cout_p * kpad;
+#pragma unroll 8
+    for (int sp = ls; sp < nsplit; sp += 16) s += (double)p[sp * st];
+  } else if (e < total) {
+    for (int sp = ls; sp < nsplit; sp += 16) s += bpart[(size_t)sp * cout_p + (e - nW)];
   }
-}
-
-// one workgroup per output channel: db[co] = sum_p dY[p][co] (bf16 dY)
-__global__ __launch_bounds__(256) void k_bias_grad(const bf16_t* __restrict__ dY, int npix,
-                                                   int cout_p, float* __restrict__ gb,
-                                                   int accumulate) {
-  __shared__ double sh[1][kBlock / 64];
-  const int co = blockIdx.x;
-  double a[1] = {0.0};
-  for (int p = threadIdx.x; p < npix; p += kBlock) a[0] += (double)bf2f(dY[(size_t)p * cout_p + co]);
-  Reducer<0u, 1>::block(a, sh);
-  if (threadIdx.x == 0) gb[co] = accumulate ? gb[co] + (float)a[0] : (float)a[0];
+  sh[ls][le] = s;
+  __syncthreads();
+  if (ls == 0 && e < total) {
+    for (int q = 1; q < 16; ++q) s += sh[q][le];
+    gW[e] = accumulate ? gW[e] + (float)s : (float)s;
+  }
 }
 
 // 2x average pooling (bf16 in and out, FP32 sum); d is the coarse grid
@@ -905,13 +1044,12 @@ __device__ __forceinline__ void store_rows(const f32x4 (&acc)[RY], float bz, uns
 // when they fit there, else from global memory.  Each wave computes one 16-channel
 // tile of the output channels: with 32 outputs, waves 0-1 and 2-3 take the
 // same rows for the two channel tiles.
-template <int CIN, int CA, int COUT, int KCH>
+template <int CIN, int CA, int COUT>
 struct ConvZ {
   static constexpr int RY = 4;                        // output rows per wave
   static constexpr int NT = COUT / 16;                // output channel tiles
   static constexpr int WG = 4 / NT;                   // waves per channel tile, stacked in y
   static constexpr int TX = 16, TY = WG * RY;         // workgroup tile
-  static constexpr int KC = KCH;                      // output planes per workgroup
   static constexpr int CF = CIN - CA;                 // fine channels
   static constexpr int NCH = (3 * CIN + 31) / 32;     // K chunks of one input row
   static constexpr int HX = TX + 2, HY = TY + 2;      // staged fine plane (one-cell halo)
@@ -928,14 +1066,14 @@ struct ConvZ {
   static_assert(CF % 8 == 0 && CA % 8 == 0 && COUT % 16 == 0 && COUT <= 64, "layout");
 };
 
-template <int CIN, int CA, int COUT, int KCH>
+template <int CIN, int CA, int COUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_z(
-    CnnDims d, CnnDims dc, const bf16_t* __restrict__ X,
+    CnnDims d, CnnDims dc, int kc, const bf16_t* __restrict__ X,
                                                 const bf16_t* __restrict__ A,
                                                 const bf16_t* __restrict__ Wz,
                                                 const float* __restrict__ bias,
                                                 bf16_t* __restrict__ Y) {
-  using T = ConvZ<CIN, CA, COUT, KCH>;
+  using T = ConvZ<CIN, CA, COUT>;
   constexpr int RY = T::RY, NT = T::NT, NCH = T::NCH;
   __shared__ __attribute__((aligned(16))) unsigned char sm[T::LDS];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -944,7 +1082,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   const int ntx = (d.nx + T::TX - 1) / T::TX, nty = (d.ny + T::TY - 1) / T::TY;
   const int b = xcd_block();
   const int x0 = (b % ntx) * T::TX, y0 = ((b / ntx) % nty) * T::TY;
-  const int k0 = (b / (ntx * nty)) * T::KC, k1 = min(k0 + T::KC, d.nz);
+  const int k0 = (b / (ntx * nty)) * kc, k1 = min(k0 + kc, d.nz);
   const int cx0 = (x0 - 1) >> 1, cy0 = (y0 - 1) >> 1;  // coarse origin of the staged plane
   if constexpr (T::BL)
     for (int e = threadIdx.x; e < T::NB * 64; e += 256)
@@ -1100,12 +1238,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 }
 
-template <int CIN, int CA, int COUT, int KCH>
-int convz_tiles(const CnnDims& d) {
-  using T = ConvZ<CIN, CA, COUT, KCH>;
-  return ((d.nx + T::TX - 1) / T::TX) * ((d.ny + T::TY - 1) / T::TY) * ((d.nz + T::KC - 1) / T::KC);
-}
-
 // Layer 0 in 3D as a z-march (2 real input channels, 4 bytes per staged cell).
 // A wave owns 4 output rows of 16 cells; one MFMA's K covers the nine (dx, dy)
 // taps of one z tap: lane group g < 3 holds the three x taps x 2 channels of
@@ -1113,7 +1245,7 @@ int convz_tiles(const CnnDims& d) {
 // of K is zero.  Each A operand serves the three z taps: MFMAs into the
 // accumulators of planes z - 1, z, z + 1.  W0z holds the three B operands.
 struct Conv0Z {
-  static constexpr int RY = 4, TX = 16, TY = 4 * RY, KC = 32;
+  static constexpr int RY = 4, TX = 16, TY = 4 * RY;
   static constexpr int HX = TX + 2, HY = TY + 2, HP = HX * HY;
   static constexpr int NL = (HP + 255) / 256;
 };
@@ -1123,7 +1255,7 @@ struct Conv0Z {
 // the pooling kernel: each lane holds two x pairs of its channel in the rows
 // of its y pairs, and the planes of a z pair come one after the other.
 template <bool POOL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_conv0z(CnnDims d, const uint32_t* __restrict__ X2,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_conv0z(CnnDims d, int kc, const uint32_t* __restrict__ X2,
                                                 const bf16_t* __restrict__ W0z,
                                                 const float* __restrict__ bias,
                                                 bf16_t* __restrict__ Y, bf16_t* __restrict__ P0) {
@@ -1136,7 +1268,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int ntx = (d.nx + T::TX - 1) / T::TX, nty = (d.ny + T::TY - 1) / T::TY;
   const int b = xcd_block();
   const int x0 = (b % ntx) * T::TX, y0 = ((b / ntx) % nty) * T::TY;
-  const int k0 = (b / (ntx * nty)) * T::KC, k1 = min(k0 + T::KC, d.nz);
+  const int k0 = (b / (ntx * nty)) * kc, k1 = min(k0 + kc, d.nz);
   bf16x8 bw[3];  // dz = -1, 0, +1
 #pragma unroll
   for (int i = 0; i < 3; ++i) bw[i] = load8(W0z + (size_t)(i * 64 + lane) * 8);
@@ -1184,7 +1316,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
       aP[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bw[0], aP[j], 0, 0, 0);
     }
   };
-  static_assert(RY % 2 == 0 && T::KC % 2 == 0 && T::TX % 4 == 0, "pooling pairs inside a wave");
+  static_assert(RY % 2 == 0 && T::TX % 4 == 0, "pooling pairs inside a wave");
   float ps[RY / 2][2];  // pooled sums of this lane: [y pair][x pair]
   bf16_t kept[RY][4];   // the lane's bf16 outputs of the plane
   auto pool = [&](int zo) {
@@ -1247,11 +1379,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
 }
 
-int conv0z_tiles(const CnnDims& d) {
-  using T = Conv0Z;
-  return ((d.nx + T::TX - 1) / T::TX) * ((d.ny + T::TY - 1) / T::TY) * ((d.nz + T::KC - 1) / T::KC);
-}
-
 // layer 0 z-march weights: fragment dz + 1 holds, for lane 16 g + n,
 // B[k = 8 g + i][n] = W[n][tap(dx, dy = g - 1, dz)][ch] with i = 2 (dx + 1) + ch
 // for g < 3, i < 6; 0 elsewhere
@@ -1312,48 +1439,55 @@ void conv_fwd(const Cnn& n, int layer, const bf16_t* X, const bf16_t* A, void* Y
 #define GEA_CONV(CI, CO, CAA)                                                                   \
   hipLaunchKernelGGL((k_conv_t<NDIM, CI, CO, CAA>), dim3(conv_tiles<NDIM, CI>(d)), bl, 0, s, d, X, \
                      A, n.W[layer], n.bias[layer], (bf16_t*)Y)
+#define GEA_CONVZ(CI, CAA, CO, KC0, COARSE, AIN)                                                  \
+  do {                                                                                            \
+    using T = ConvZ<CI, CAA, CO>;                                                                 \
+    const ConvPlan q = conv_plan(d, T::TX, T::TY, KC0, 2);                                        \
+    hipLaunchKernelGGL((k_conv_z<CI, CAA, CO>), dim3(q.blocks), bl, 0, s, d, COARSE, q.kc, X, AIN, \
+                       n.Wz[layer], n.bias[layer], (bf16_t*)Y);                                   \
+  } while (0)
   switch (layer) {
     case 0:
-      if constexpr (NDIM == 3)
-      {
+      if constexpr (NDIM == 3) {
+        const ConvPlan q = conv_plan(d, Conv0Z::TX, Conv0Z::TY, 32, 4, 2);
         if (pooled)
-          hipLaunchKernelGGL(k_conv0z<true>, dim3(conv0z_tiles(d)), bl, 0, s, d, (const uint32_t*)n.x2,
+          hipLaunchKernelGGL(k_conv0z<true>, dim3(q.blocks), bl, 0, s, d, q.kc, (const uint32_t*)n.x2,
                              n.W0z, n.bias[0], (bf16_t*)Y, pooled);
         else
-          hipLaunchKernelGGL(k_conv0z<false>, dim3(conv0z_tiles(d)), bl, 0, s, d, (const uint32_t*)n.x2,
+          hipLaunchKernelGGL(k_conv0z<false>, dim3(q.blocks), bl, 0, s, d, q.kc, (const uint32_t*)n.x2,
                              n.W0z, n.bias[0], (bf16_t*)Y, pooled);
-      }
-      else
+      } else {
         hipLaunchKernelGGL((k_conv0<NDIM>), dim3(conv_tiles<NDIM, 8>(d)), bl, 0, s, d,
                            (const uint32_t*)n.x2, n.W0, n.bias[0], (bf16_t*)Y);
+      }
       break;
     case 1:
       if constexpr (NDIM == 3)
-        hipLaunchKernelGGL((k_conv_z<16, 0, 32, 16>), dim3(convz_tiles<16, 0, 32, 16>(d)), bl, 0, s, d, d,
-                           X, X, n.Wz[1], n.bias[1], (bf16_t*)Y);
+        GEA_CONVZ(16, 0, 32, 16, d, X);
       else
         GEA_CONV(16, 32, 0);
       break;
     case 2: GEA_CONV(32, 64, 0); break;
     case 3:
       if constexpr (NDIM == 3)
-        hipLaunchKernelGGL((k_conv_z<96, 64, 32, 16>), dim3(convz_tiles<96, 64, 32, 16>(d)), bl, 0, s, d,
-                           n.d[L.level + 1], X, A, n.Wz[3], n.bias[3], (bf16_t*)Y);
+        GEA_CONVZ(96, 64, 32, 16, n.d[L.level + 1], A);
       else
         GEA_CONV(96, 32, 64);
       break;
     case 4:
       if constexpr (NDIM == 3)
-        hipLaunchKernelGGL((k_conv_z<48, 32, 16, 64>), dim3(convz_tiles<48, 32, 16, 64>(d)), bl, 0, s, d,
-                           n.d[L.level + 1], X, A, n.Wz[4], n.bias[4], (bf16_t*)Y);
+        GEA_CONVZ(48, 32, 16, 64, n.d[L.level + 1], A);
       else
         GEA_CONV(48, 16, 32);
       break;
-    case 5:
-      hipLaunchKernelGGL((k_conv5z<NDIM>), dim3(conv5z_tiles<NDIM>(d)), bl, 0, s, d, X,
+    case 5: {
+      const ConvPlan q = conv_plan(d, Conv5Z<NDIM>::TX, Conv5Z<NDIM>::TY, 16, 4);
+      hipLaunchKernelGGL((k_conv5z<NDIM>), dim3(q.blocks), bl, 0, s, d, q.kc, X,
                          (const uint32_t*)n.W5, n.bias[5], (float*)Y, scale);
       break;
+    }
   }
+#undef GEA_CONVZ
 #undef GEA_CONV
 }
 
@@ -1381,10 +1515,11 @@ template <int NDIM>
 void conv_wgrad(const Cnn& n, int layer, const bf16_t* X, const bf16_t* dYq, bool acc) {
   const CnnLayer& L = n.L[layer];
   const CnnDims& d = n.d[L.level];
-  const int nsplit = (d.npix + kPixPerSplit - 1) / kPixPerSplit;
-  const dim3 gr((L.kpad / 16 + 3) / 4, nsplit), bl(256);
+  const WgradPlan w = wgrad_plan(d, NDIM, L.cin_p);
+  const dim3 gr((L.cin_p + 15) / 16, w.nsplit), bl(256);
   hipStream_t s = n.s;
-#define GEA_WG(CI, CO) hipLaunchKernelGGL((k_wgrad<NDIM, CI, CO>), gr, bl, 0, s, d, X, dYq, n.part)
+#define GEA_WG(CI, CO) \
+  hipLaunchKernelGGL((k_wgrad<NDIM, CI, CO>), gr, bl, 0, s, d, w, X, dYq, n.part, n.bpart)
   switch (layer) {
     case 0: GEA_WG(8, 16); break;
     case 1: GEA_WG(16, 32); break;
@@ -1395,11 +1530,10 @@ void conv_wgrad(const Cnn& n, int layer, const bf16_t* X, const bf16_t* dYq, boo
   }
 #undef GEA_WG
   const int ntaps = NDIM == 2 ? 9 : 27;
-  const long nW = (long)L.cout * ntaps * L.cin;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks_for(nW)), bl, 0, s, (const float*)n.part, nsplit,
-                     L.cout_p, L.kpad, L.cin, L.cin_p, L.cout, ntaps, n.grad + L.woff, (int)acc);
-  hipLaunchKernelGGL(k_bias_grad, dim3(L.cout), bl, 0, s, dYq, d.npix, L.cout_p, n.grad + L.boff,
-                     (int)acc);
+  const int nout = L.cout * ntaps * L.cin + L.cout;  // the bias follows the weights
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((nout + 15) / 16), bl, 0, s, (const float*)n.part,
+                     (const double*)n.bpart, w.nsplit, L.cout_p, L.kpad, L.cin, L.cin_p, L.cout,
+                     ntaps, n.grad + L.woff, (int)acc);
 }
 
 // the forward convolution of one layer on the network's own buffers
@@ -1592,15 +1726,16 @@ size_t cnn_carve(Cnn& n, int ndim, int nx, int ny, int nz, bool train, char* bas
     n.q2 = (bf16_t*)take(N2 * 64 * B2);
     n.q1 = (bf16_t*)take(N1 * 32 * B2);
     n.q0 = (bf16_t*)take(N0 * 16 * B2);
-    long mx = 0;
+    long mx = 0, mb = 0;
     for (int l = 0; l < kCnnLayers; ++l) {
       const CnnLayer& L = n.L[l];
-      const long ns = (n.d[L.level].npix + kPixPerSplit - 1) / kPixPerSplit;
+      const long ns = wgrad_plan(n.d[L.level], ndim, L.cin_p).nsplit;
       const long need = ns * L.cout_p * L.kpad;
       if (need > mx) mx = need;
+      if (ns * L.cout_p > mb) mb = ns * L.cout_p;
     }
-    n.part_floats = mx;
     n.part = (float*)take((size_t)mx * F4);
+    n.bpart = (double*)take((size_t)mb * sizeof(double));
     n.lpart = (double*)take(sizeof(double) * 1024);
   }
   return off;

@@ -38,8 +38,6 @@ struct Cnn {
   CnnDims d[3];
   CnnLayer L[kCnnLayers];
   long nparams = 0;
-  int nsplit = 1;        // pixel splits of the weight-gradient reduction
-  long part_floats = 0;  // size of that reduction's partial buffer
   // parameters
   float* master = nullptr;
   float* grad = nullptr;
@@ -60,7 +58,8 @@ struct Cnn {
   // backward
   float *t, *dy5, *dd0, *dc0, *dd1, *de0, *dc1, *de2, *de1, *dp1, *dp0;
   bf16_t *q5, *q4, *q3, *q2, *q1, *q0;  // bf16 copies of the (masked) output gradients
-  float* part;
+  float* part;    // weight-gradient partials of the splits
+  double* bpart;  // bias-gradient partials
   double* lpart;
 };
 
