@@ -1,4 +1,4 @@
-// gea_cgp.hip -- a whole Jacobi-PCG solve of a 2D system in one launch.
+// gea_cgp.hip -- a whole Jacobi-PCG solve in one launch.
 //
 // A workgroup keeps its tile of the solve's vectors on the chip (registers,
 // and LDS where the registers do not hold them) from the first iteration to
@@ -126,6 +126,9 @@ __device__ __forceinline__ double waves_sum(double v) {
   v = halve<16>(v, v);
   return halve<32>(v, v);
 }
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
+}
 __device__ __forceinline__ double lane_value(double v, int l) {
   return join(__builtin_amdgcn_readlane(half_of(v, 0), l), __builtin_amdgcn_readlane(half_of(v, 1), l));
 }
@@ -144,6 +147,74 @@ struct Wait {
     return now > end;
   }
 };
+
+// The sums of all workgroups' eight values from this workgroup's per wave
+// (sh_w), in every thread: a workgroup's sums are one 128-byte line of `set`,
+// lane l holds half l % 2 of value l % 16 / 2.  True when a wait outlasted its
+// limit.  (A barrier has made sh_w visible; eight waves.)
+__device__ __forceinline__ bool sums_of_all(const double (&sh_w)[8][8], double (&sh_s)[8][8],
+                                            uint64_t* set, int nblk, uint32_t tag, uint64_t spin,
+                                            int* sh_dead, double (&s7)[7]) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double tot = waves_sum(sh_w[lane >> 3][lane & 7]);  // value l % 8 in lane l
+  if (nblk > 1) {
+    uint64_t* const st = set + (lane & 15);
+    if (w == 0) {
+      const double v8 = __shfl(tot, (lane & 15) >> 1, 64);
+      if (lane < 16) word_store(st + 16L * blockIdx.x, tag, half_of(v8, lane & 1));
+    }
+    // every workgroup's sums: four lines a load, wave w the lines 4 w ..
+    // of each 32, four such loads in flight
+    double sum = 0.0;
+    bool late = false;
+    for (int b = w * 4 + (lane >> 4); b < nblk; b += 128) {
+      const uint64_t* const from = st + 16L * b;
+      uint64_t dw[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) dw[u] = word_load(from + (b + 32 * u < nblk ? 512 * u : 0));
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        for (Wait wt; (uint32_t)(dw[u] >> 32) != tag;
+             dw[u] = word_load(from + (b + 32 * u < nblk ? 512 * u : 0)))
+          if (wt.over(spin)) {
+            late = true;
+            break;
+          }
+        // (even lanes: the other half is their neighbour's)
+        const uint32_t own = (uint32_t)dw[u];
+        const uint32_t other = __builtin_amdgcn_update_dpp(0u, own, 0xb1, 0xf, 0xf, false);
+        if (b + 32 * u < nblk) sum += join(own, other);
+      }
+    }
+    sum = halve<32>(sum, sum);
+    sum = halve<16>(sum, sum);
+    if (lane < 16 && (lane & 1) == 0) sh_s[w][lane >> 1] = sum;
+    if (late) *sh_dead = 1;
+    lds_barrier();
+    tot = waves_sum(sh_s[lane >> 3][lane & 7]);
+  }
+#pragma unroll
+  for (int u = 0; u < 7; ++u) s7[u] = lane_value(tot, u);
+  return *sh_dead != 0;
+}
+
+// what a solve leaves (one thread a workgroup)
+__device__ __forceinline__ void leave_scalars(CgScalars* sc, uint64_t* ex, int status, int iter,
+                                              double rr, bool bad, bool corrects, uint32_t base) {
+  if (status == kCgpAborted) {  // (any workgroup may be the one that waited too long)
+    __hip_atomic_store(&sc->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else if (blockIdx.x == 0) {
+    sc->iter = iter + 1;
+    sc->rr = rr;
+    sc->fin = bad ? 0 : 1;
+    sc->done_iter = iter + 1;
+    if (corrects && !bad) sc->corrected = 1;
+    sc->status = status;
+    __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    word_store(ex, 0u, base + 1u + (uint32_t)iter);
+  }
+}
 
 // T, CD: precision; D constant (CgVectors::D null).  R: rows a thread holds.
 // NW: waves.  XL: x and c live in LDS.  The tile: 64 wx columns by R NW / wx
@@ -271,7 +342,6 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
     hw[s] = (owner * EW + e) * NH;
   }
   const long epar = (long)nblk * EW * NH, spar = 16L * nblk;  // words of one parity
-  const int lane_set = CD ? (t & 15) : (lane & 15);
   uint64_t* const my_edge = edges + (long)tile * EW * NH;
   const double tolbb = sc->tol2 * sc->bb;
   const int max_iter = sc->max_iter;
@@ -375,10 +445,10 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
     const double ws = wave_sum8(acc);
     if ((lane & 7) == 0) sh_w[w][lane >> 3] = ws;
     lds_barrier();
-    uint64_t* const st = sets + (iter & 1) * spar + lane_set;
     double s7[7];
-    bool late = false;
     if constexpr (CD) {
+      uint64_t* const st = sets + (iter & 1) * spar + (t & 15);
+      bool late = false;
       // the tree of k_cg_iter2 and its sum over partials: the four waves in
       // order, then workgroup b in thread b (b - 256, ...) of four waves
       double sum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -412,45 +482,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
       for (int u = 0; u < 7; ++u) s7[u] = ((sh_s[0][u] + sh_s[1][u]) + sh_s[2][u]) + sh_s[3][u];
     } else {
       static_assert(CD || NW == 8, "one value of one wave a lane");
-      double tot = waves_sum(sh_w[lane >> 3][lane & 7]);  // value l % 8 in lane l
-      if (nblk > 1) {
-        // a workgroup's sums are one 128-byte line: lane l holds half l % 2
-        // of value l % 16 / 2
-        if (w == 0) {
-          const double v8 = __shfl(tot, (lane & 15) >> 1, 64);
-          if (lane < 16) word_store(st + 16L * blockIdx.x, tag, half_of(v8, lane & 1));
-        }
-        // every workgroup's sums: four lines a load, wave w the lines 4 w ..
-        // of each 32, four such loads in flight
-        double sum = 0.0;
-        for (int b = w * 4 + (lane >> 4); b < nblk; b += 128) {
-          const uint64_t* const from = st + 16L * b;
-          uint64_t dw[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) dw[u] = word_load(from + (b + 32 * u < nblk ? 512 * u : 0));
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            for (Wait wt; (uint32_t)(dw[u] >> 32) != tag;
-                 dw[u] = word_load(from + (b + 32 * u < nblk ? 512 * u : 0)))
-              if (wt.over(g.spin)) {
-                late = true;
-                break;
-              }
-            // (even lanes: the other half is their neighbour's)
-            const uint32_t own = (uint32_t)dw[u];
-            const uint32_t other = __builtin_amdgcn_update_dpp(0u, own, 0xb1, 0xf, 0xf, false);
-            if (b + 32 * u < nblk) sum += join(own, other);
-          }
-        }
-        sum = halve<32>(sum, sum);
-        sum = halve<16>(sum, sum);
-        if (lane < 16 && (lane & 1) == 0) sh_s[w][lane >> 1] = sum;
-        if (late) sh_dead = 1;
-        lds_barrier();
-        tot = waves_sum(sh_s[lane >> 3][lane & 7]);
-      }
-#pragma unroll
-      for (int u = 0; u < 7; ++u) s7[u] = lane_value(tot, u);
+      if constexpr (!CD) sums_of_all(sh_w, sh_s, sets + (iter & 1) * spar, nblk, tag, g.spin, &sh_dead, s7);
     }
     if (sh_dead) {
       bad = true;
@@ -530,20 +562,568 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
       }
     }
   }
-  if (t != 0) return;
-  if (status == kCgpAborted) {  // (any workgroup may be the one that waited too long)
-    __hip_atomic_store(&sc->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else if (blockIdx.x == 0) {
-    sc->iter = iter + 1;
-    sc->rr = rr;
-    sc->fin = bad ? 0 : 1;
-    sc->done_iter = iter + 1;
-    if (v.xo && !bad) sc->corrected = 1;
-    sc->status = status;
-    __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    word_store(g.ex, 0u, base + 1u + (uint32_t)iter);
+  if (t == 0) leave_scalars(sc, g.ex, status, iter, rr, bad, v.xo != nullptr, base);
+}
+
+// ---- 3D --------------------------------------------------------------------------
+// The same solve of a 3D system.  A workgroup's tile is 64 x (8 RY) x RZ
+// cells; wave w holds rows RY w .. of every plane, a thread a column of RZ
+// cells in each of its RY rows.  The direction lives in LDS with a one-cell
+// halo (the halo below and above in registers: those cells' thread is the
+// column's own), r, A p and 1/diag in registers.  What holds the rest:
+//  - MEM false: x and c in registers, D in LDS, nothing moves through memory;
+//  - MEM true (64 cells a thread): D and c are read, x read and written each
+//    iteration, 16 bytes a cell where the iteration kernel moves 44.
+// And what the neighbours exchange:
+//  - HQ true: A p, as in k_cgp2: the halo's r, p and 1/diag are kept by the
+//    thread that stages it, and one exchange an iteration is enough;
+//  - HQ false: the new direction, a second exchange behind the sums', where
+//    the halo's vectors would not fit the registers.
+template <typename T, int RY, int RZ, bool MEM, bool HQ>
+__global__ __launch_bounds__(512) void k_cgp3(Geo G, Stencil<3, T> K, CgSolve<T> v, CgpGrid g,
+                                              CgScalars* sc) {
+  constexpr int NW = 8, NT = 512, NH = sizeof(T) / 4, TY = RY * NW, TZ = RZ, R = RY * RZ;
+  constexpr int SX = 66, SY = TY + 2;
+  constexpr int ZE = TY * 64, YE = TZ * 64, XE = TY * TZ;  // border cells of a z, y, x side
+  constexpr int EW = 2 * (ZE + YE + XE);
+  constexpr int NZ = 2 * RY, NY = (2 * YE + NT - 1) / NT, NHC = NZ + NY + (2 * XE + NT - 1) / NT;
+  __shared__ T sp[TZ * SY * SX];
+  __shared__ T sd[MEM ? 1 : TZ * SY * SX];
+  __shared__ T zl[MEM ? NZ * NT : 1];
+  __shared__ double sh_w[NW][8], sh_s[NW][8];
+  __shared__ int sh_dead;
+  if (__hip_atomic_load(&sc->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || sc->bb == 0.0) return;
+  const int nx = G.nx, ny = G.ny, nz = G.nz;
+  const int tile = xcd_block(), nblk = gridDim.x;
+  const int bx = tile % g.nbx, by = (tile / g.nbx) % g.nby, bz = tile / (g.nbx * g.nby);
+  const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int i0 = bx * 64, j0 = by * TY, k0 = bz * TZ, i = i0 + lane;
+  const uint32_t base = (uint32_t)word_load(g.ex);  // (the previous launch left it)
+  uint64_t* const edges = g.ex + 8;
+  const long epar = (long)nblk * EW * NH, spar = 16L * nblk;  // words of one parity
+  uint64_t* const sets = edges + 2 * epar;
+  const bool in = i < nx;
+  const T hx = T(0.5) * K.k[0], hy = T(0.5) * K.k[1], kz = T(0.5) * K.k[2];
+  const T kxr = i + 1 < nx ? hx : T(0), kxl = in && i > 0 ? hx : T(0);
+  // weights of the faces below the wave's rows and above the last (no face on the walls)
+  T ky[RY + 1];
+#pragma unroll
+  for (int jy = 0; jy <= RY; ++jy) {
+    const int gj = j0 + w * RY + jy;
+    ky[jy] = gj > 0 && gj < ny ? hy : T(0);
   }
+  // (half the constant: the same bits as 0.5 (a + b) k)
+  auto weight = [](T a, T b, T half_k) { return (a + b) * half_k; };
+  auto at = [](int k, int y, int x) { return (k * SY + y + 1) * SX + x + 1; };
+  // the thread's own cell of plane 0 and its first row; other cells are
+  // constants away.  (This, the thread index of the halo, the plane's size and
+  // the tile's first plane are made opaque in each iteration: addresses kept from one to the next
+  // would take the registers of the vectors.)
+  int own = at(0, w * RY, lane), th = t, plane = nx * ny, kb = k0;
+  auto off = [](int k, int y, int x) { return (k * SY + y) * SX + x; };
+  if (t == 0) sh_dead = 0;
+  for (int e = t; e < TZ * SY * SX; e += NT) {
+    sp[e] = T(0);
+    if constexpr (!MEM) sd[e] = T(0);
+  }
+  __syncthreads();
+
+  // ---- halo cells of this thread: [0, NZ) below and above its columns, then
+  // of the y sides, then of the x sides
+  struct Halo {
+    bool ok;
+    int P, word, dst;  // cell; its owner's border word (parity 0); place in sp
+  };
+  auto halo = [&](int s) {
+    Halo h;
+    asm volatile("" : "+v"(th));  // (one cell's arithmetic after the other's)
+    const int l = th & 63;
+    int hi = i0 + l, hj, hk, owner, e;
+    bool ok = true;
+    if (s < NZ) {
+      const int up = s / RY, y = w * RY + s % RY;
+      hj = j0 + y;
+      hk = up ? k0 + TZ : k0 - 1;
+      owner = tile + (up ? 1 : -1) * g.nbx * g.nby;
+      e = (up ? 0 : ZE) + y * 64 + l;
+      h.dst = 0;
+    } else if (s < NZ + NY) {
+      const int e0 = th + NT * (s - NZ), up = e0 >= YE, rem = e0 - up * YE, k = rem >> 6;
+      ok = e0 < 2 * YE;
+      hj = up ? j0 + TY : j0 - 1;
+      hk = k0 + k;
+      owner = tile + (up ? 1 : -1) * g.nbx;
+      e = 2 * ZE + (up ? 0 : YE) + rem;
+      h.dst = at(k, up ? TY : -1, l);
+    } else {
+      const int e0 = th + NT * (s - NZ - NY), up = e0 >= XE, rem = e0 - up * XE, y = rem % TY, k = rem / TY;
+      ok = e0 < 2 * XE;
+      hi = up ? i0 + 64 : i0 - 1;
+      hj = j0 + y;
+      hk = k0 + k;
+      owner = tile + (up ? 1 : -1);
+      e = 2 * (ZE + YE) + (up ? 0 : XE) + rem;
+      h.dst = at(k, y, up ? 64 : -1);
+    }
+    h.ok = ok && hi >= 0 && hi < nx && hj >= 0 && hj < ny && hk >= 0 && hk < nz;
+    h.P = h.ok ? hi + nx * hj + plane * hk : 0;
+    h.word = (h.ok ? owner * EW + e : tile * EW + l) * NH;  // (no cell: a word that is not waited for)
+    return h;
+  };
+
+  // ---- the tile's vectors: cells outside the mesh hold zeros throughout
+  T r[R], q[R], m[R], x[MEM ? 1 : R], c[MEM ? 1 : R];
+  // direction below [0, RY) and above the thread's columns
+  T zr[MEM ? 1 : NZ];
+  auto zh_get = [&](int s) { return MEM ? zl[MEM ? s * NT + th : 0] : zr[MEM ? 0 : s]; };
+  auto zh_put = [&](int s, T val) {
+    if constexpr (MEM)
+      zl[s * NT + th] = val;
+    else
+      zr[s] = val;
+  };
+  // weight of the lowest faces, D above the highest cells (MEM: read each iteration)
+  T wz0[MEM ? 1 : RY], dt[MEM ? 1 : RY];
+  const int ic = in ? i : nx - 1;
+  // (uniform) start of the wave's row jy of plane k, clamped into the mesh
+  int rows[RY + 2];
+#pragma unroll
+  for (int jy = -1; jy <= RY; ++jy) {
+    const int gj = j0 + w * RY + jy;
+    rows[jy + 1] = nx * (gj < 0 ? 0 : (gj < ny ? gj : ny - 1));
+  }
+  auto row_of = [&](int k, int jy) {
+    const int gk = kb + k;
+    return rows[jy + 1] + plane * (gk < 0 ? 0 : (gk < nz ? gk : nz - 1));
+  };
+  auto live_row = [&](int k, int jy) { return j0 + w * RY + jy < ny && kb + k < nz; };
+  // a value of that row: scalar base, 32-bit offset of the lane
+  uint32_t ib = (uint32_t)ic * sizeof(T);
+  auto st = [&](T* f, int k, int jy, T val) {
+    typedef __attribute__((address_space(1))) char* gchar;
+    gchar row = (gchar)(f + row_of(k, jy));
+    asm volatile("" : "+s"(row), "+v"(ib));
+    *(__attribute__((address_space(1))) T*)(row + ib) = val;
+  };
+  auto ld = [&](const T* f, int k, int jy) {
+    typedef const __attribute__((address_space(1))) char* gchar;
+    gchar row = (gchar)(f + row_of(k, jy));
+    asm volatile("" : "+s"(row), "+v"(ib));  // (or the address becomes a 64-bit vector sum)
+    return *(const __attribute__((address_space(1))) T*)(row + ib);
+  };
+  double r_r = 0.0, r_z = 0.0;  // this thread's (r, r) and (r, z)
+#pragma unroll
+  for (int k = 0; k < RZ; ++k) {
+#pragma unroll
+    for (int jy = 0; jy < RY; ++jy) {
+      const int n = k * RY + jy, y = w * RY + jy;
+      const bool ok = in && live_row(k, jy);
+      const T rv = ld(v.r, k, jy), mv = ld(v.dinv, k, jy);
+      r[n] = ok ? rv : T(0);
+      m[n] = ok ? mv : T(0);
+      q[n] = T(0);
+      if constexpr (!MEM) {
+        const T cv = ld(v.c, k, jy);
+        x[n] = ld(v.x, k, jy);
+        c[n] = ok ? cv : T(0);
+        sd[at(k, y, lane)] = ld(v.D, k, jy);
+      }
+      const T z = r[n] * m[n];
+      sp[at(k, y, lane)] = z;
+      r_r += (double)r[n] * (double)r[n];
+      r_z += (double)r[n] * (double)z;
+    }
+    if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (!MEM) {
+#pragma unroll
+    for (int jy = 0; jy < RY; ++jy) {
+      wz0[jy] = k0 > 0 ? weight(ld(v.D, -1, jy), ld(v.D, 0, jy), kz) : T(0);
+      dt[jy] = ld(v.D, TZ, jy);
+    }
+  }
+  // (MEM) of plane k in lane k: D right of the tile's rows, weight of their left faces
+  T er[RY], el[RY];
+  if constexpr (MEM) {
+    static_assert(RZ <= 64, "a plane a lane");
+#pragma unroll
+    for (int jy = 0; jy < RY; ++jy) {
+      const T* const row = v.D + row_of(lane < RZ ? lane : 0, jy);
+      er[jy] = row[i0 + 64 < nx ? i0 + 64 : nx - 1];
+      el[jy] = i0 > 0 ? weight(row[i0 > 0 ? i0 - 1 : 0], row[i0], hx) : T(0);
+    }
+  }
+  T hr[HQ ? NHC : 1], hp[HQ ? NHC : 1], hm[HQ ? NHC : 1];
+#pragma unroll
+  for (int s = 0; s < NHC; ++s) {
+    const Halo h = halo(s);
+    const T rv = v.r[h.P], mv = v.dinv[h.P];
+    const T pv = h.ok ? rv * mv : T(0);
+    if constexpr (HQ) {
+      hr[s] = rv;
+      hm[s] = mv;
+      hp[s] = pv;
+    }
+    if (s < NZ)
+      zh_put(s, pv);
+    else if (h.ok) {
+      sp[h.dst] = pv;
+      if constexpr (!MEM) sd[h.dst] = v.D[h.P];
+    }
+  }
+  __syncthreads();
+  uint64_t* const my_edge = edges + (long)tile * EW * NH;
+  // border words of the neighbours: scalar base, 32-bit offset
+  auto edge_load = [&](int iter, int word) {
+    typedef const __attribute__((address_space(1))) char* gchar;
+    gchar from = (gchar)(edges + (iter & 1) * epar);
+    uint32_t o = (uint32_t)word * 8u;
+    asm volatile("" : "+s"(from), "+v"(o));
+    return __hip_atomic_load((const __attribute__((address_space(1))) uint64_t*)(from + o), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto publish = [&](uint64_t* o, int e, uint32_t tag, T val) {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) word_store(o + e * NH + h, tag, half_of(val, h));
+  };
+  // (uniform) neighbours in z
+  const bool zl_nb = bz > 0, zh_nb = k0 + TZ < nz;
+  const double tolbb = sc->tol2 * sc->bb;
+  const int max_iter = sc->max_iter;
+  constexpr int GX = R < 8 ? R : 8;  // x of these cells in flight (MEM)
+  // (MEM) one load of a wave that names 64 of the 128-byte lines it reads later:
+  // it brings them into the L2 in the meantime, for one register.  D and c of
+  // WIN planes from plane k on, or x of 2 WIN planes.
+  constexpr int WIN = 8;
+  static_assert(!MEM || (RY * WIN * 4 == 64 && RZ == 4 * WIN && sizeof(T) == 4), "a line a lane");
+  auto touch_row = [&](const T* f, int k, int n) {
+    const int row = n % RY ? rows[RY] : rows[1], gk = kb + k + n / RY, gx = i0 + 32 * (th & 1);
+    return f[row + plane * (gk < nz ? gk : nz - 1) + (gx < nx ? gx : nx - 1)];
+  };
+  auto touch = [&](int k) { return touch_row(th & 32 ? v.D : v.c, k, (th & 31) >> 1); };
+  auto touch_x = [&](int k) { return touch_row(v.x, k, (th & 63) >> 1); };
+  T line = T(0), line_x[2] = {T(0), T(0)};
+  T alpha, beta;
+  double rr = 0.0;
+  int iter = 0, status = 0;
+  bool bad = false;
+  for (;; ++iter) {
+    const uint32_t tag = base + 1u + (uint32_t)iter;
+    asm volatile("" : "+v"(own), "+v"(th), "+s"(plane), "+s"(kb));
+    // ---- A p and the dots, plane by plane
+    // ((r, r) and (r, z) are summed where r is formed)
+    double acc[8] = {0.0, 0.0, 0.0, r_r, 0.0, 0.0, r_z, 0.0};
+    {
+      // D and c around plane k that its step reads
+      struct Set {
+        T da[RY], dl[MEM ? 1 : RY], dr[MEM ? 1 : RY], c[RY], dlo, dhi;
+      };
+      auto load = [&](int k) {
+        Set f;
+#pragma unroll
+        for (int jy = 0; jy < RY; ++jy) {
+          if constexpr (MEM) {
+            f.c[jy] = ld(v.c, k, jy);
+            f.da[jy] = ld(v.D, k + 1, jy);
+          } else {
+            f.dl[jy] = sd[own + off(k, jy, -1)];
+            f.dr[jy] = sd[own + off(k, jy, 1)];
+            f.c[jy] = c[k * RY + jy];
+            f.da[jy] = k + 1 < RZ ? sd[own + off(k + 1, jy, 0)] : dt[jy];
+          }
+        }
+        if constexpr (MEM) {
+          f.dlo = ld(v.D, k, -1);
+          f.dhi = ld(v.D, k, RY);
+        } else {
+          f.dlo = sd[own + off(k, -1, 0)];
+          f.dhi = sd[own + off(k, RY, 0)];
+        }
+        return f;
+      };
+      T pb[RY], pc[RY], dc[RY], wb[RY];
+#pragma unroll
+      for (int jy = 0; jy < RY; ++jy) {
+        pb[jy] = zh_get(jy);
+        pc[jy] = sp[own + off(0, jy, 0)];
+        dc[jy] = MEM ? ld(v.D, 0, jy) : sd[MEM ? 0 : own + off(0, jy, 0)];
+        wb[jy] = MEM ? weight(ld(v.D, -1, jy), dc[jy], k0 > 0 ? kz : T(0)) : wz0[MEM ? 0 : jy];
+      }
+      Set cur = load(0);
+      int pl = own;  // (own cell of every eighth plane: LDS offsets are 16 bits)
+#pragma unroll
+      for (int k = 0; k < RZ; ++k) {
+        if (k % 8 == 0 && k > 0) {
+          pl += off(8, 0, 0);
+          asm volatile("" : "+v"(pl));
+        }
+        Set nxt;
+        if (k + 1 < RZ) nxt = load(k + 1);
+        if constexpr (MEM) {
+          if (k % WIN == 0 && k + WIN < RZ) line = touch(k + WIN);
+        }
+        const T kzu = kb + k + 1 < nz ? kz : T(0);
+        const T plo = sp[pl + off(k % 8, -1, 0)], phi = sp[pl + off(k % 8, RY, 0)];
+        T wlo = weight(cur.dlo, dc[0], ky[0]);
+#pragma unroll
+        for (int jy = 0; jy < RY; ++jy) {
+          const int n = k * RY + jy;
+          const T pr = sp[pl + off(k % 8, jy, 1)], pf = sp[pl + off(k % 8, jy, -1)];
+          const T pu = jy + 1 < RY ? pc[jy + 1 < RY ? jy + 1 : 0] : phi;
+          const T pd = jy > 0 ? pc[jy > 0 ? jy - 1 : 0] : plo;
+          const T pa = k + 1 < RZ ? sp[pl + off(k + 1 < RZ ? k % 8 + 1 : 0, jy, 0)] : zh_get(RY + jy);
+          T wr, wl;
+          if constexpr (MEM) {
+            wr = weight(dc[jy], lane_next<true>(lane_value(er[jy], k), dc[jy]), kxr);
+            wl = lane_next<false>(lane_value(el[jy], k), wr);
+          } else {
+            wr = weight(dc[jy], cur.dr[jy], kxr);
+            wl = weight(cur.dl[jy], dc[jy], kxl);
+          }
+          const T wu = weight(dc[jy], jy + 1 < RY ? dc[jy + 1 < RY ? jy + 1 : 0] : cur.dhi, ky[jy + 1]);
+          const T wa = weight(dc[jy], cur.da[jy], kzu);
+          const T p0 = pc[jy];
+          T a = cur.c[jy] * p0;
+          a = fma_t(p0 - pr, wr, a);
+          a = fma_t(p0 - pf, wl, a);
+          a = fma_t(p0 - pu, wu, a);
+          a = fma_t(p0 - pd, wlo, a);
+          a = fma_t(p0 - pa, wa, a);
+          a = fma_t(p0 - pb[jy], wb[jy], a);
+          q[n] = a;
+          asm volatile("" : "+v"(m[n]));  // (r m formed anew: kept it is a register more a cell)
+          const T z = r[n] * m[n], mq = a * m[n];
+          acc[0] += (double)p0 * (double)a;
+          acc[1] += (double)a * (double)z;
+          acc[2] += (double)a * (double)mq;
+          acc[4] += (double)a * (double)r[n];
+          acc[5] += (double)a * (double)a;
+          // (summed here, not gathered behind the planes)
+          if constexpr (MEM)
+            asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[4]), "+v"(acc[5]));
+          wlo = wu;
+          wb[jy] = wa;
+          pb[jy] = pa;  // (swapped below: the row above still reads pc)
+        }
+#pragma unroll
+        for (int jy = 0; jy < RY; ++jy) {
+          const T up = pb[jy];
+          pb[jy] = pc[jy];
+          pc[jy] = up;
+          dc[jy] = cur.da[jy];
+        }
+        if (k + 1 < RZ) cur = nxt;
+        if constexpr (MEM) {
+          if (k % WIN == WIN - 1) asm volatile("" ::"v"(line));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if constexpr (HQ) {
+      if (nblk > 1) {
+        uint64_t* const me = my_edge + (iter & 1) * epar;
+#pragma unroll
+        for (int jy = 0; jy < RY; ++jy) {
+          const int y = w * RY + jy;
+          if (zl_nb) publish(me, y * 64 + lane, tag, q[jy]);
+          if (zh_nb) publish(me, ZE + y * 64 + lane, tag, q[(RZ - 1) * RY + jy]);
+        }
+        if (w == 0 && by > 0) {
+#pragma unroll
+          for (int k = 0; k < RZ; ++k) publish(me, 2 * ZE + k * 64 + lane, tag, q[k * RY]);
+        }
+        if (w == NW - 1 && by + 1 < g.nby) {
+#pragma unroll
+          for (int k = 0; k < RZ; ++k) publish(me, 2 * ZE + YE + k * 64 + lane, tag, q[k * RY + RY - 1]);
+        }
+        if ((lane == 0 && bx > 0) || (lane == 63 && bx + 1 < g.nbx)) {
+          const int side = lane == 0 ? 0 : XE;
+#pragma unroll
+          for (int n = 0; n < R; ++n)
+            publish(me, 2 * (ZE + YE) + side + (n / RY) * TY + w * RY + n % RY, tag, q[n]);
+        }
+      }
+    }
+    // (MEM) the first x of the update, in flight while the sums arrive
+    T xg[MEM ? GX : 1];
+    if constexpr (MEM) {
+      line_x[0] = touch_x(0);
+      line_x[1] = touch_x(2 * WIN);
+#pragma unroll
+      for (int n = 0; n < GX; ++n) xg[n] = ld(v.x, n / RY, n % RY);
+    }
+    // ---- the sums of all workgroups
+    const double ws = wave_sum8(acc);
+    if ((lane & 7) == 0) sh_w[w][lane >> 3] = ws;
+    lds_barrier();
+    double s7[7];
+    const bool late = sums_of_all(sh_w, sh_s, sets + (iter & 1) * spar, nblk, tag, g.spin, &sh_dead, s7);
+    if (late) {
+      bad = true;
+      status = kCgpAborted;
+      break;
+    }
+    const StepScalars o = scalars_of(s7, iter, tolbb, max_iter);
+    alpha = (T)o.alpha;
+    beta = (T)o.beta;
+    if (o.bad || o.fin) {
+      status = o.status;
+      bad = o.bad;
+      rr = o.rr;
+      break;
+    }
+    asm volatile("" : "+v"(own), "+v"(th), "+s"(plane), "+s"(kb));
+    // ---- the update (every wave is past its reads of sp: the sums' barrier)
+    uint64_t hv[HQ ? NHC : 1][NH];
+    if constexpr (HQ) {  // the halo's A p meanwhile
+#pragma unroll
+      for (int s = 0; s < NHC; ++s) {
+        const Halo h = halo(s);
+#pragma unroll
+        for (int u = 0; u < NH; ++u) hv[s][u] = edge_load(iter, h.word + u);
+      }
+    }
+    uint64_t* const me = my_edge + (iter & 1) * epar;
+    r_r = r_z = 0.0;
+    int pl = own;  // (own cell of every eighth plane: LDS offsets are 16 bits)
+#pragma unroll
+    for (int n0 = 0; n0 < R; n0 += GX) {
+      T xn[MEM ? GX : 1];
+      if constexpr (MEM) {
+        if (n0 + GX < R) {
+#pragma unroll
+          for (int u = 0; u < GX; ++u) {
+            const int n = n0 + GX + u;
+            xn[u] = ld(v.x, n / RY, n % RY);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < GX; ++u) {
+        const int n = n0 + u, k = n / RY, jy = n % RY;
+        if (n % (8 * RY) == 0 && n > 0) {
+          pl += off(8, 0, 0);
+          asm volatile("" : "+v"(pl));
+        }
+        const T pv = sp[pl + off(k % 8, jy, 0)];
+        if constexpr (MEM) {
+          const T xv = fma_t(pv, alpha, xg[u]);
+          if (in && live_row(k, jy)) st(v.x, k, jy, xv);
+        } else {
+          x[n] = fma_t(pv, alpha, x[n]);
+        }
+        r[n] = fma_t(-q[n], alpha, r[n]);
+        const T z = r[n] * m[n];
+        r_r += (double)r[n] * (double)r[n];
+        r_z += (double)r[n] * (double)z;
+        asm volatile("" : "+v"(r_r), "+v"(r_z));  // (here, not gathered behind the update)
+        const T pn = fma_t(pv, beta, z);
+        sp[pl + off(k % 8, jy, 0)] = pn;
+        if constexpr (!HQ) {  // what the neighbours below and above read
+          if (k == 0 && zl_nb) publish(me, (w * RY + jy) * 64 + lane, tag, pn);
+          if (k == RZ - 1 && zh_nb) publish(me, ZE + (w * RY + jy) * 64 + lane, tag, pn);
+        }
+      }
+      if constexpr (MEM) {
+#pragma unroll
+        for (int u = 0; u < GX; ++u) xg[u] = xn[u];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("" : "+v"(own), "+v"(th), "+s"(plane), "+s"(kb));
+    if constexpr (MEM) {
+      asm volatile("" ::"v"(line_x[0]), "v"(line_x[1]));
+      line = touch(0);
+    }
+    // ---- the halo
+    if constexpr (!HQ) {
+      lds_barrier();  // the own cells' new direction
+      if (nblk > 1) {  // (by all waves: two of them alone took 14 us more for the y sides)
+#pragma unroll
+        for (int u = 0; u < NY; ++u) {
+          const int e0 = th + NT * u, up = e0 >= YE, rem = e0 - up * YE;
+          if (e0 < 2 * YE && (up ? by + 1 < g.nby : by > 0))
+            publish(me, 2 * ZE + e0, tag, sp[at(rem >> 6, up ? TY - 1 : 0, th & 63)]);
+        }
+#pragma unroll
+        for (int u = 0; u < NHC - NZ - NY; ++u) {
+          const int e0 = th + NT * u, up = e0 >= XE, rem = e0 - up * XE;
+          if (e0 < 2 * XE && (up ? bx + 1 < g.nbx : bx > 0))
+            publish(me, 2 * (ZE + YE) + e0, tag, sp[at(rem / TY, rem % TY, up ? 63 : 0)]);
+        }
+      }
+    }
+    constexpr int GH = HQ ? NHC : 7;  // halo words in flight a thread
+#pragma unroll
+    for (int s0 = 0; s0 < NHC; s0 += GH) {
+      uint64_t wv[HQ ? 1 : GH][NH];
+      if constexpr (!HQ) {
+#pragma unroll
+        for (int s = s0; s < s0 + GH && s < NHC; ++s) {
+          const Halo h = halo(s);
+#pragma unroll
+          for (int u = 0; u < NH; ++u) wv[s - s0][u] = edge_load(iter, h.word + u);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+#pragma unroll
+      for (int s = s0; s < s0 + GH && s < NHC; ++s) {
+        const Halo h = halo(s);
+        if (!h.ok) continue;
+        uint64_t(&hw)[NH] = HQ ? hv[HQ ? s : 0] : wv[HQ ? 0 : s - s0];
+        for (Wait wt;;) {
+          bool ok = true;
+#pragma unroll
+          for (int u = 0; u < NH; ++u) ok = ok && (uint32_t)(hw[u] >> 32) == tag;
+          if (ok) break;
+          if (wt.over(g.spin)) {
+            sh_dead = 1;
+            break;
+          }
+#pragma unroll
+          for (int u = 0; u < NH; ++u) hw[u] = edge_load(iter, h.word + u);
+        }
+        T hval;
+        if constexpr (NH == 1)
+          hval = __uint_as_float((uint32_t)hw[0]);
+        else
+          hval = __longlong_as_double((hw[NH - 1] << 32) | (uint32_t)hw[0]);
+        if constexpr (HQ) {
+          hr[s] = fma_t(-hval, alpha, hr[s]);
+          hp[s] = fma_t(hp[s], beta, hr[s] * hm[s]);
+          hval = hp[s];
+        }
+        if (s < NZ)
+          zh_put(s, hval);
+        else
+          sp[h.dst] = hval;
+        if constexpr (!HQ) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    lds_barrier();
+  }
+  // the last update (none after a non-finite value)
+  if (status != kCgpAborted) {
+#pragma unroll
+    for (int n = 0; n < R; ++n) {
+      const int k = n / RY, jy = n % RY;
+      if (in && live_row(k, jy)) {
+        const int P = row_of(k, jy) + i;
+        T xv;
+        if constexpr (MEM)
+          xv = v.x[P];
+        else
+          xv = x[n];
+        if (!bad) xv = fma_t(sp[own + off(k, n % RY, 0)], alpha, xv);
+        if (v.xo && !bad)
+          v.xo[P] += (double)xv;
+        else
+          v.x[P] = xv;
+      }
+      if (n % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if (t == 0) leave_scalars(sc, g.ex, status, iter, rr, bad, v.xo != nullptr, base);
 }
 
 // ---- plans -----------------------------------------------------------------------
@@ -556,22 +1136,38 @@ void launch(hipStream_t s, const Geo& G, const CgSolve<T>& v, const CgpPlan& p, 
   hipLaunchKernelGGL((k_cgp2<T, CD, R, NW, XL>), dim3(p.blocks), dim3(64 * NW), 0, s, G, K, v, g, sc);
 }
 
-// the kernels: (precision, constant D, rows, waves, x and c in LDS)
+template <typename T, int RY, int RZ, bool MEM, bool HQ>
+void launch3(hipStream_t s, const Geo& G, const CgSolve<T>& v, const CgpPlan& p, const CgpGrid& g,
+             CgScalars* sc) {
+  Stencil<3, T> K;
+  for (int d = 0; d < 3; ++d) K.k[d] = (T)(G.S[d] / G.h[d]);
+  hipLaunchKernelGGL((k_cgp3<T, RY, RZ, MEM, HQ>), dim3(p.blocks), dim3(512), 0, s, G, K, v, g, sc);
+}
+
+// the kernels: (precision, constant D, rows, waves, x and c in LDS) in 2D,
+// (precision, y rows, planes, vectors in memory, A p exchanged) in 3D
 template <typename T>
 struct Variant {
+  int ndim;
   bool cd;
-  int rows, waves;
+  int rows, waves;  // 2D: rows a thread; 3D: y rows of the tile, planes
   const void* fn;
   void (*run)(hipStream_t, const Geo&, const CgSolve<T>&, const CgpPlan&, const CgpGrid&, CgScalars*);
 };
 #define GEA_CGP(T, CD, R, NW, XL) \
-  { CD, R, NW, (const void*)&k_cgp2<T, CD, R, NW, XL>, &launch<T, CD, R, NW, XL> }
+  { 2, CD, R, NW, (const void*)&k_cgp2<T, CD, R, NW, XL>, &launch<T, CD, R, NW, XL> }
+#define GEA_CGP3(T, RY, RZ, MEM, HQ) \
+  { 3, false, 8 * RY, RZ, (const void*)&k_cgp3<T, RY, RZ, MEM, HQ>, &launch3<T, RY, RZ, MEM, HQ> }
 const Variant<double> kV64[] = {
     GEA_CGP(double, true, 16, 4, false),
     GEA_CGP(double, false, 2, 8, false),
     GEA_CGP(double, false, 4, 8, false),
     GEA_CGP(double, false, 8, 8, false),
     GEA_CGP(double, false, 16, 8, true),
+    GEA_CGP3(double, 1, 2, false, true),
+    GEA_CGP3(double, 1, 4, false, true),
+    GEA_CGP3(double, 1, 8, false, true),
+    GEA_CGP3(double, 2, 8, false, false),
 };
 const Variant<float> kV32[] = {
     GEA_CGP(float, false, 2, 8, false),
@@ -579,6 +1175,11 @@ const Variant<float> kV32[] = {
     GEA_CGP(float, false, 8, 8, false),
     GEA_CGP(float, false, 16, 8, false),
     GEA_CGP(float, false, 32, 8, true),
+    GEA_CGP3(float, 1, 2, false, true),
+    GEA_CGP3(float, 1, 4, false, true),
+    GEA_CGP3(float, 2, 8, false, true),
+    GEA_CGP3(float, 2, 16, false, false),
+    GEA_CGP3(float, 2, 32, true, false),
 };
 template <typename T>
 const Variant<T>* variants(int* n);
@@ -599,8 +1200,22 @@ const Variant<float>* variants<float>(int* n) {
 template <typename T>
 CgpPlan tiles(const Geo& G, const Variant<T>& V) {
   CgpPlan p{};
+  if (G.ndim != V.ndim) return p;
+  if (G.ndim == 3) {
+    const int ty = V.rows, tz = V.waves;
+    p.wx = 1;
+    p.nbx = (G.nx + 63) / 64;
+    p.nby = (G.ny + ty - 1) / ty;
+    const long n = (long)p.nbx * p.nby * ((G.nz + tz - 1) / tz);
+    // (tiles of 64 x 16 x 16 cells and more leave no LDS for a second workgroup)
+    if (n > (ty * tz < 256 ? kMaxCgpBlocks : kCus)) return p;
+    p.blocks = (int)n;
+    p.words = 8 + 2L * n * 2 * (64 * ty + 64 * tz + ty * tz) * (long)(sizeof(T) / 4) + 2L * 16 * n;
+    return p;
+  }
   long blocks = 0;
   int tz = 0;
+  p.nby = 1;
   for (int wx = V.cd ? 4 : 1; wx <= 4; wx *= 2) {
     const int h = V.rows * V.waves / wx, nbx = (G.nx + 64 * wx - 1) / (64 * wx);
     const long n = (long)nbx * ((G.nz + h - 1) / h);
@@ -619,12 +1234,12 @@ CgpPlan tiles(const Geo& G, const Variant<T>& V) {
 
 }  // namespace
 
-// The plan of the one-launch solve: the variant with the fewest rows a thread
-// whose workgroups are all on the card at once.  The constant-D system (the
+// The plan of the one-launch solve: the variant with the fewest cells a thread
+// whose workgroups are all on the card at once.  (3D meshes of more than
+// 256 tiles of 64 x 16 x 32 cells in FP32, 64 x 16 x 8 in FP64, have none.)  The constant-D system (the
 // energy solves) has one variant, its tiles and sums those of k_cg_iter2.
 template <typename T>
 CgpPlan cgp_plan(const Geo& G, bool cd) {
-  if (G.ndim != 2) return CgpPlan{};
   int dev = 0, cus = 0, n = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
@@ -637,13 +1252,13 @@ CgpPlan cgp_plan(const Geo& G, bool cd) {
     CgpPlan p = tiles(G, V[k]);
     int per = 0;
     if (p.blocks == 0) continue;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, V[k].fn, 64 * V[k].waves, 0) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, V[k].fn, V[k].ndim == 3 ? 512 : 64 * V[k].waves, 0) != hipSuccess) {
       (void)hipGetLastError();
       continue;
     }
     if (p.blocks > (long)cus * per) continue;
     // (a single workgroup exchanges nothing: worth twice the rows, not more)
-    if (!cd && p.blocks > 1 && k + 1 < n && V[k + 1].rows <= 4 && tiles(G, V[k + 1]).blocks == 1) continue;
+    if (!cd && G.ndim == 2 && p.blocks > 1 && k + 1 < n && V[k + 1].rows <= 4 && tiles(G, V[k + 1]).blocks == 1) continue;
     p.variant = k + 1;
     return p;
   }
@@ -664,7 +1279,6 @@ static long words_of(const Geo& G) {
   return most;
 }
 long cgp_words(const Geo& G) {
-  if (G.ndim != 2) return 0;
   const long a = words_of<double>(G), b = words_of<float>(G);
   return a > b ? a : b;
 }
@@ -677,7 +1291,7 @@ void cgp_solve(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgpPlan
   int n = 0;
   const Variant<T>& V = variants<T>(&n)[p.variant - 1];
   const CgSolve<T> a{v.x, v.r, v.c, v.D, v.dinv, v.Dc, v.xo};
-  const CgpGrid g{ex, spin, p.wx, p.nbx};
+  const CgpGrid g{ex, spin, p.wx, p.nbx, p.nby};
   V.run(s, G, a, p, g, sc);
 }
 template void cgp_solve<double>(hipStream_t, const Geo&, const CgVectors<double>&, const CgpPlan&, uint64_t*, uint64_t, CgScalars*);

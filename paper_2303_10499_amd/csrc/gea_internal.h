@@ -245,7 +245,7 @@ void cg_scalars(hipStream_t s, const Geo& G, int iter, const CgWork& w);
 bool cg_folds(const CgWork& w);
 // ---- one-launch solves (gea_cgp.hip) -----------------------------------------
 // A whole solve set up as for cg_iter_kernel (residual in v.r, initial x,
-// scalars in sc) in one launch, for 2D meshes whose workgroups fit the card
+// scalars in sc) in one launch, for meshes whose workgroups fit the card
 // at once (plan.variant 0: they do not).  It leaves the scalars as the
 // iteration kernels do (done, iter, rr, status, corrected); a system with
 // ||b|| = 0 or done already is left alone.
@@ -259,7 +259,7 @@ constexpr uint64_t kCgpSpin = 25000000ull;  // 0.25 s of the 100 MHz clock
 constexpr int kSharedBlocks = 48;
 struct CgpPlan {
   int variant;  // 1 + index of the kernel, 0: none
-  int wx, nbx, blocks;
+  int wx, nbx, nby, blocks;
   long words;   // 64-bit words of the exchange area, zero before its first launch
 };
 template <typename T>
@@ -275,7 +275,7 @@ struct CgSolve {
 struct CgpGrid {
   uint64_t* ex;   // the exchange area; word 0: the last tag used
   uint64_t spin;
-  int wx, nbx;
+  int wx, nbx, nby;
 };
 template <typename T>
 CgpPlan cgp_plan(const Geo& G, bool cd);
