@@ -226,7 +226,9 @@ struct gea_ctx {
   // implicit transport (transport = 1): BiCGStab vectors and scalars
   TrVecs trv{};
   double* trb[3] = {nullptr, nullptr, nullptr};  // the predictor systems' right-hand sides
-  TrScalars* tsc = nullptr;
+  TrScalars* tsc = nullptr;     // kTrSlots of them
+  double* tr_part = nullptr;
+  int last_tr[4] = {};  // iterations of the last transport solve: u components, T
   Cnn net;             // network at the mesh resolution (learned form only)
   bool has_net_space = false;
   bool has_net = false;
@@ -396,11 +398,12 @@ size_t carve(Carver& cv, gea_ctx* x, const gea_mesh& m, bool learned, bool trans
   x->sc = cv.take<CgScalars>(1);
   x->sc32 = cv.take<CgScalars>(1);
   x->fsc = cv.take<FcgScalars>(1);
-  x->tsc = cv.take<TrScalars>(1);
+  x->tsc = cv.take<TrScalars>(kTrSlots);
   if (transport)
     for (double** a : {&x->trv.b, &x->trv.dinv, &x->trv.r, &x->trv.rh, &x->trv.p, &x->trv.v,
                        &x->trv.y, &x->trv.z, &x->trv.t})
       *a = cv.take<double>(nc);
+  if (transport) x->tr_part = cv.take<double>((size_t)tr_part_doubles(make_geo(m)));
   if (transport)
     for (int d = 0; d < nd; ++d) x->trb[d] = cv.take<double>(nc);
   // partials: 7 per workgroup of the iteration kernel's grid, in two sets
@@ -1241,21 +1244,20 @@ TrOp energy_op(const gea_ctx* x, const State& S, bool enth) {
   return op;
 }
 
-// One BiCGStab solve behind its enqueued set-up: iterations in batches
-// (doubling up to 16), the scalars read once a batch.
-gea_status bicg_run(gea_ctx* x, const TrOp& op, double* xv, int* iters) {
+// One BiCGStab solve behind its enqueued set-up: iterations in batches (the
+// first as long as the last solve of this unknown was, then doubling up to
+// 16), the scalars read once a batch.
+gea_status bicg_run(gea_ctx* x, const TrOp& op, double* xv, int unknown, int* iters) {
   const Geo& G = x->G;
-  x->timer.run(7, x->stream, [&] {
-    launch_tr_start(x->stream, G, op, x->partials, kTransportTol, x->prm.max_iter, x->tsc);
-  });
   TrScalars hs{};
-  int batch = 2;
+  int& last = x->last_tr[unknown];
+  int batch = last > 0 ? last : 2, next = last > 0 ? 2 : 4;
   long launched = 0;
   for (;;) {
-    for (int k = 0; k < batch; ++k)
-      x->timer.run(7, x->stream, [&] {
-        launch_tr_iteration(x->stream, G, op, xv, x->trv, x->partials, x->tsc);
-      });
+    x->timer.run(7, x->stream, [&] {
+      launch_tr_iterations(x->stream, G, op, xv, x->trv, x->tr_part, x->tsc, kTransportTol,
+                           x->prm.max_iter, batch, launched == 0);
+    });
     HIPCHK(hipGetLastError());
     launched += batch;
     const Extra part{x->tsc, &hs, sizeof hs};
@@ -1265,8 +1267,10 @@ gea_status bicg_run(gea_ctx* x, const TrOp& op, double* xv, int* iters) {
       x->err = "implicit transport solve: the solver never finished";
       return GEA_ERR_NOCONV;
     }
-    batch = batch < 16 ? 2 * batch : 16;
+    batch = next;
+    next = next < 16 ? 2 * next : 16;
   }
+  last = hs.status == 0 ? hs.iter : 0;
   if (hs.bb == 0.0) launch_fill(x->stream, G, xv, 0.0);  // b = 0: x = 0
   *iters = hs.iter;
   if (hs.status == 0) return GEA_OK;
@@ -1303,9 +1307,9 @@ gea_status steps_1_2(gea_ctx* x, const State& S, double* T_out, double* pp_out =
       const TrOp op = momentum_op(x, S, d);
       TrVecs v = x->trv;
       v.b = x->trb[d];
-      x->timer.run(7, x->stream, [&] { launch_tr_setup_mom(s, G, op, x->ustar[d], v, x->partials); });
+      x->timer.run(7, x->stream, [&] { launch_tr_setup_mom(s, G, op, x->ustar[d], v, x->tr_part); });
       int its = 0;
-      gea_status rc = bicg_run(x, op, x->ustar[d], &its);
+      gea_status rc = bicg_run(x, op, x->ustar[d], d, &its);
       if (transport_iters) *transport_iters += its;
       if (rc != GEA_OK) return rc;
     }
@@ -1321,10 +1325,10 @@ gea_status steps_1_2(gea_ctx* x, const State& S, double* T_out, double* pp_out =
     const TrOp op = energy_op(x, S, enth);
     x->timer.run(7, x->stream, [&] {
       launch_tr_setup_energy(s, G, ph, enth, op, S.rho, x->e0, x->ustar, x->ea, S.T, x->Tbg, T_out,
-                             x->trv, x->partials);
+                             x->trv, x->tr_part);
     });
     int its = 0;
-    gea_status rc = bicg_run(x, op, T_out, &its);
+    gea_status rc = bicg_run(x, op, T_out, 3, &its);
     if (transport_iters) *transport_iters += its;
     if (rc != GEA_OK) return rc;
     x->timer.run(5, x->stream, [&] {

@@ -339,21 +339,30 @@ struct TrScalars {
   double bb, rr, rr0, rho, rho_old, alpha, omega, beta, tol2;
   int iter, max_iter, status, done;  // status 0 ok, -4 no convergence or breakdown, -5 non-finite
 };
+// per-workgroup partials of the solve's stages: nz operator workgroups, nb of
+// the vector passes
+struct TrParts {
+  double *rhv, *ts, *ss, *rhr, *setup;
+  int nz, nb, max_iter;
+  double tol;
+};
 // set-up of a momentum component (x0: the initial guess; v.b the right-hand
 // side V (rho^n u^n/dt - R(F^n)) from Step 1's pass) or of the energy solve
 // (writes the known transported part into w and T^n into x); each stores 2
-// partials a workgroup (zplan(G).blocks workgroups) for launch_tr_start
+// partials a workgroup for the first iteration
 void launch_tr_setup_mom(hipStream_t s, const Geo& G, const TrOp& op, const double* x0,
                          const TrVecs& v, double* part);  // v.b: the component's right-hand side
 void launch_tr_setup_energy(hipStream_t s, const Geo& G, const Phys& ph, bool enth, const TrOp& op,
                             const double* rho, const double* e0, double* const* u_star,
                             double* w, const double* Tn, const double* Tbg, double* x,
                             const TrVecs& v, double* part);
-void launch_tr_start(hipStream_t s, const Geo& G, const TrOp& op, const double* part, double tol, int max_iter,
-                     TrScalars* sc);
-// one BiCGStab iteration (nine launches; all return at once once sc->done)
-void launch_tr_iteration(hipStream_t s, const Geo& G, const TrOp& op, double* x, const TrVecs& v,
-                         double* part, TrScalars* sc);
+// the first or the next n BiCGStab iterations behind the set-up (five launches
+// each; all return at once when the solve is done) and one kernel that leaves
+// the scalars in slots[0] for the host
+void launch_tr_iterations(hipStream_t s, const Geo& G, const TrOp& op, double* x, const TrVecs& v,
+                          double* part, TrScalars* slots, double tol, int max_iter, int n, bool first);
+constexpr int kTrSlots = 5;
+long tr_part_doubles(const Geo& G);  // size of the partials area of the functions above
 // relative residual of the implicit-transport solves
 constexpr double kTransportTol = 1e-13;
 // a solve's scalars from the set-up partials another kernel formed (nu
