@@ -406,14 +406,13 @@ size_t carve(Carver& cv, gea_ctx* x, const gea_mesh& m, bool learned, bool trans
   if (transport) x->tr_part = cv.take<double>((size_t)tr_part_doubles(make_geo(m)));
   if (transport)
     for (int d = 0; d < nd; ++d) x->trb[d] = cv.take<double>(nc);
-  // partials: 7 per workgroup of the iteration kernel's grid, in two sets
-  // (by iteration parity); 2 (and 1 for ||b||^2) per workgroup of the set-up
+  // partials: 7 per workgroup of the iteration kernel's grid (7 a wave where
+  // their sums are formed apart), in two sets (by iteration parity); 2 (and 1 for ||b||^2) per workgroup of the set-up
   // kernels' column-tile grid
   const Geo G = make_geo(m);
-  const int ns = std::max({iter_grid<double>(G), iter_grid<double>(G, true), iter_grid<float>(G)});
   const int nzb = zmax_blocks(zplan(make_geo(m)));
   for (CgWork* w : {&x->w64, &x->w32}) {
-    w->s = cv.take<double>(14 * (size_t)ns);
+    w->s = cv.take<double>((size_t)iter_partials(G));
     w->u[0] = nullptr;
     w->u[1] = cv.take<double>(2 * (size_t)nzb);
     w->b = cv.take<double>(nzb);
@@ -1193,7 +1192,7 @@ gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters
       [&](int j, bool fold, bool last) {
         x->timer.run(7, x->stream, [&] {
           cg_iter_kernel<double>(x->stream, G, v, j, w, fold);
-          if (last || !cg_folds(w)) cg_scalars(x->stream, G, j, w);
+          if (last || !cg_folds(w)) cg_scalars(x->stream, G, j, w, true);
         });
       });
   if (rc != GEA_OK) return rc;

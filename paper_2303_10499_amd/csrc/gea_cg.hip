@@ -46,6 +46,8 @@
 // mapped so that each XCD (own L2) works on a contiguous block of tiles.  The
 // same kernels instantiated on float, with FP64 dot accumulation, are the
 // inner solver of the mixed-precision refinement.
+#include <algorithm>
+
 #include "gea_reduce.h"
 
 namespace gea {
@@ -75,8 +77,9 @@ constexpr int kKC2 = sizeof(T) == 8 ? 16 : 32;
 
 // sum of n partials, identical in every workgroup; result in all threads.
 // (Unrolling keeps each thread's order of additions: U only trades
-// registers for loads in flight.  LDSB: barriers that order LDS only.)
-template <int N, int U = 8, bool LDSB = false>
+// registers for loads in flight.  LDSB: barriers that order LDS only.  W: a
+// partial is W waves' values, added in wave order.)
+template <int N, int U = 8, bool LDSB = false, int W = 1>
 __device__ __forceinline__ void sum_partials(const double* __restrict__ part, int n,
                                              double (&out)[N]) {
   __shared__ double sh[N][kBlock / 64];
@@ -86,7 +89,12 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ part, in
 #pragma unroll U
   for (int b = threadIdx.x; b < n; b += kBlock) {
 #pragma unroll
-    for (int k = 0; k < N; ++k) a[k] += part[k * n + b];
+    for (int k = 0; k < N; ++k) {
+      double p = part[(long)(k * n + b) * W];
+#pragma unroll
+      for (int w = 1; w < W; ++w) p += part[(long)(k * n + b) * W + w];
+      a[k] += p;
+    }
   }
   if constexpr (LDSB)
     Reducer<0u, N>::block_lds(a, sh);
@@ -119,20 +127,6 @@ __device__ __forceinline__ bool gate_closed(const CgScalars* gate) {
          __hip_atomic_load(&gate->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
 }
 
-// the partials of iteration `iter` within the parity-buffered set
-__device__ __forceinline__ double* iter_part(double* part, int ns, int iter) {
-  return part + (iter & 1) * 7L * ns;
-}
-
-// the scalars of iteration `iter` from its ns partials; every thread of every
-// workgroup that forms them gets the same values
-__device__ __forceinline__ StepScalars step_scalars(const double* part, int ns, int iter,
-                                                    const CgScalars* sc) {
-  double s[7];
-  // (few registers, and the iteration kernels' first loads stay in flight)
-  sum_partials<7, 2, true>(part, ns, s);
-  return scalars_of(s, iter, sc->tol2 * sc->bb, sc->max_iter);
-}
 
 // (one thread) the scalars of iteration `iter` for the host and the next
 // kernels
@@ -154,7 +148,28 @@ struct CgStep {
   int ns;
   int iter;
   int fold;
+  int dots;  // 0: the partials are another kernel's (k_cg_dots3), one a wave
 };
+
+// the partials of iteration `iter` within the parity-buffered set
+__device__ __forceinline__ double* iter_part(const CgStep& st, int iter) {
+  return st.part + (iter & 1) * (st.dots ? 7L : 28L) * st.ns;
+}
+
+// the scalars of iteration `iter` from its ns partials; every thread of every
+// workgroup that forms them gets the same values.  (APART: the partials may be
+// k_cg_dots3's)
+template <bool APART>
+__device__ __forceinline__ StepScalars step_scalars(const CgStep& st, int iter, const CgScalars* sc) {
+  const double* const part = iter_part(st, iter);
+  double s[7];
+  // (few registers, and the iteration kernels' first loads stay in flight)
+  if (!APART || st.dots)
+    sum_partials<7, 2, true>(part, st.ns, s);
+  else
+    sum_partials<7, 2, true, 4>(part, st.ns, s);
+  return scalars_of(s, iter, sc->tol2 * sc->bb, sc->max_iter);
+}
 
 // Whether an iteration kernel has work: false once the solve is done or an
 // earlier launch of its batch ended it.  Within a launch only done_iter
@@ -170,11 +185,11 @@ __device__ __forceinline__ bool step_live(const CgStep& st, CgScalars* sc) {
 // The update an iteration kernel applies (alpha, beta of the iteration
 // before it) and whether it is the solve's last; false: return at once.
 // The kernels call it after issuing their first loads.
-template <typename T>
+template <bool APART = false, typename T>
 __device__ __forceinline__ bool step_take(const CgStep& st, CgScalars* sc, T& alpha, T& beta,
                                           int& fin) {
   if (st.fold) {
-    const StepScalars o = step_scalars(iter_part(st.part, st.ns, st.iter - 1), st.ns, st.iter - 1, sc);
+    const StepScalars o = step_scalars<APART>(st, st.iter - 1, sc);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       publish(o, st.iter - 1, sc);
       if (o.bad)  // a non-finite value ends the solve without this update
@@ -298,14 +313,14 @@ __global__ __launch_bounds__(kBlock) void k_cg_start(const double* u_part, int n
 
 // one workgroup after iteration `iter`: alpha, the residual after the
 // update, beta and the stop test (see the file header)
-__global__ __launch_bounds__(kBlock) void k_cg_scalars(double* part, int ns, int iter,
-                                                       CgScalars* sc) {
+__global__ __launch_bounds__(kBlock) void k_cg_scalars(CgStep st, CgScalars* sc) {
+  const int iter = st.iter;
   if (load_done(sc)) return;
   if (sc->done_iter >= 0) {  // a launch of the batch ended the solve
     if (threadIdx.x == 0) __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return;
   }
-  const StepScalars o = step_scalars(iter_part(part, ns, iter), ns, iter, sc);
+  const StepScalars o = step_scalars<true>(st, iter, sc);
   if (threadIdx.x != 0) return;
   publish(o, iter, sc);
   if (o.bad) __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -540,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_iter3(Geo G, Stencil<3, T> K, CgI
   }
   // the scalars, while the first planes' loads are in flight
   int fin;
-  if (!step_take(stp, sc, alpha, beta, fin)) return;
+  if (!step_take<CD>(stp, sc, alpha, beta, fin)) return;
   if (fin) {  // the solve has converged: its last x update only
 #pragma unroll
     for (int m = 0; m < RPT; ++m)
@@ -562,7 +577,115 @@ __global__ __launch_bounds__(kBlock) void k_cg_iter3(Geo G, Stencil<3, T> K, CgI
   } else {
     for (int kk = k0 - 1; kk <= k1; ++kk) plane_step(f0, kk);
   }
-  store_partials<7>(acc, iter_part(stp.part, stp.ns, stp.iter));
+  if (!CD || stp.dots) store_partials<7>(acc, iter_part(stp, stp.iter));
+}
+
+// The partials of k_cg_iter3<T, true> launched with fixed chunks of KC planes
+// (workgroup, thread, plane and row order), from the vectors a launch with
+// shorter chunks has stored.  Each of the seven sums is a chain over the
+// column's planes, but they do not depend on each other, nor do a workgroup's
+// four waves: each wave (blockIdx.y), and each of four sets of the sums
+// (blockIdx.z), is a workgroup here and leaves its own partial.  An energy
+// solve's iteration on 64 x 64 x 32 cells (8 workgroups of fixed chunks) took
+// 55 us in one launch and takes 7.6 + 9.8; with the sums as 8 workgroups of 4
+// or of 16 waves 7.6 + 18 or 27.
+template <typename T, int SET>
+__device__ __forceinline__ void dots_set(const Geo& G, const T (&w)[3], const CgIter<T>& v, int i, int j0,
+                                         int k0, int k1, double (&acc)[2]) {
+  constexpr int RPT = kTX3 * kTY3 / kBlock, U = 16;  // U planes in flight
+  constexpr bool kP = SET == 0, kR = SET != 3, kM = SET >= 2;
+  const int nx = G.nx, ny = G.ny, nz = G.nz, plane = nx * ny;
+  int Q[RPT];
+  bool in[RPT];
+#pragma unroll
+  for (int m = 0; m < RPT; ++m) {
+    const int j = j0 + m * (kBlock / kTX3);
+    in[m] = i < nx && j < ny;
+    Q[m] = in[m] ? i + nx * j : 0;
+  }
+  for (int kb = k0; kb < k1; kb += U) {
+    T p[U][RPT], q[U][RPT], r[U][RPT], c[U][RPT];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int m = 0; m < RPT; ++m) {
+        const int P = Q[m] + plane * min(kb + u, k1 - 1);
+        q[u][m] = v.q_out[P];
+        if (kP) p[u][m] = v.p_out[P];
+        if (kR) r[u][m] = v.r_out[P];
+        if (kM) c[u][m] = v.c[P];
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = kb + u;
+#pragma unroll
+      for (int m = 0; m < RPT; ++m) {
+        if (k >= k1 || !in[m]) continue;
+        const double a = (double)q[u][m], rd = kR ? (double)r[u][m] : 0.0;
+        T mv = T(0);
+        if (kM) {  // 1/diag as k_cg_iter3 forms it
+          const int j = j0 + m * (kBlock / kTX3);
+          T dg = c[u][m];
+          dg += i + 1 < nx ? w[0] : T(0);
+          dg += i > 0 ? w[0] : T(0);
+          dg += j + 1 < ny ? w[1] : T(0);
+          dg += j > 0 ? w[1] : T(0);
+          dg += k + 1 < nz ? w[2] : T(0);
+          dg += k > 0 ? w[2] : T(0);
+          mv = T(1) / dg;
+        }
+        // (the terms of iter_dots)
+        if (SET == 0) {
+          acc[0] += (double)p[u][m] * a;
+          acc[1] += rd * rd;
+        } else if (SET == 1) {
+          acc[0] += a * rd;
+          acc[1] += a * a;
+        } else if (SET == 2) {
+          const T z = r[u][m] * mv;
+          acc[0] += a * (double)z;
+          acc[1] += rd * (double)z;
+        } else {
+          const T mq = q[u][m] * mv;
+          acc[0] += a * (double)mq;
+        }
+      }
+    }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) void k_cg_dots3(Geo G, Stencil<3, T> K, CgIter<T> v, int KC, CgStep stp,
+                                                 CgScalars* sc) {
+  if (load_done(sc) ||
+      __hip_atomic_load(&sc->done_iter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= 0)
+    return;
+  const int ntx = (G.nx + kTX3 - 1) / kTX3, nty = (G.ny + kTY3 - 1) / kTY3;
+  const int b = xcd_block(), wave = blockIdx.y, set = blockIdx.z;
+  const int i = (b % ntx) * kTX3 + (int)threadIdx.x, j0 = ((b / ntx) % nty) * kTY3 + wave;
+  const int k0 = (b / (ntx * nty)) * KC, k1 = min(k0 + KC, G.nz);
+  const T w[3] = {v.Dc * K.k[0], v.Dc * K.k[1], v.Dc * K.k[2]};
+  double acc[2] = {0.0, 0.0};
+  int to[2];  // the partials these are
+  if (set == 0) {
+    dots_set<T, 0>(G, w, v, i, j0, k0, k1, acc);
+    to[0] = 0, to[1] = 3;
+  } else if (set == 1) {
+    dots_set<T, 1>(G, w, v, i, j0, k0, k1, acc);
+    to[0] = 4, to[1] = 5;
+  } else if (set == 2) {
+    dots_set<T, 2>(G, w, v, i, j0, k0, k1, acc);
+    to[0] = 1, to[1] = 6;
+  } else {
+    dots_set<T, 3>(G, w, v, i, j0, k0, k1, acc);
+    to[0] = 2, to[1] = -1;
+  }
+  double* const part = iter_part(stp, stp.iter);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double a = wave_sum(acc[k]);
+    if (threadIdx.x == 0 && to[k] >= 0) part[4L * (to[k] * stp.ns + blockIdx.x) + wave] = a;
+  }
 }
 
 // 2D iteration kernel: a workgroup owns a 256-cell row segment and marches it
@@ -686,7 +809,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_iter2(Geo G, Stencil<2, T> K, CgI
     mc = mn;
     cur = wn;
   }
-  store_partials<7>(acc, iter_part(stp.part, stp.ns, stp.iter));
+  store_partials<7>(acc, iter_part(stp, stp.iter));
 }
 
 template <int NDIM>
@@ -934,6 +1057,18 @@ Stencil<NDIM, T> stencil(const Geo& G) {
 
 }  // namespace
 
+// The energy solves' chunks, fixed for the order of their sums, leave CUs idle
+// on small 3D meshes: there the iteration takes the chunks that fill the card,
+// and its sums a pass of their own in the fixed order.
+static bool dots_apart(const Geo& G, bool cd) {
+  return cd && G.ndim == 3 && plan3<double>(G, false).kc < plan3<double>(G, true).kc;
+}
+
+long iter_partials(const Geo& G) {
+  const long fixed = iter_grid<double>(G, true) * (dots_apart(G, true) ? 4L : 1L);
+  return 14 * std::max({(long)iter_grid<double>(G, false), fixed, (long)iter_grid<float>(G, false)});
+}
+
 template <typename T>
 int iter_grid(const Geo& G, bool cd) {
   if (G.ndim == 3) return plan3<T>(G, cd).blocks;
@@ -975,23 +1110,28 @@ template <typename T>
 void cg_iter_kernel(hipStream_t s, const Geo& G, const CgVectors<T>& v, int iter, const CgWork& w,
                     bool fold) {
   const CgIter<T> it = iter_vectors(v, iter);
-  const CgStep stp{w.s, w.ns, iter, fold && iter > 0 && cg_folds(w) ? 1 : 0};
-  const bool cd = v.D == nullptr;
+  const bool cd = v.D == nullptr, apart = dots_apart(G, cd);
+  const CgStep stp{w.s, w.ns, iter, fold && iter > 0 && cg_folds(w) ? 1 : 0, apart ? 0 : 1};
   if (G.ndim == 2) {
     if (cd)
       hipLaunchKernelGGL((k_cg_iter2<T, true>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<2, T>(G), it, stp, w.sc);
     else
       hipLaunchKernelGGL((k_cg_iter2<T, false>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<2, T>(G), it, stp, w.sc);
   } else {
-    if (cd)
+    if (apart) {
+      const ZPlan fill = plan3<T>(G, false);
+      hipLaunchKernelGGL((k_cg_iter3<T, true>), dim3(fill.blocks), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, fill.kc, stp, w.sc);
+      hipLaunchKernelGGL(k_cg_dots3<T>, dim3(w.ns, 4, 4), dim3(64), 0, s, G, stencil<3, T>(G), it, plan3<T>(G, true).kc, stp, w.sc);
+    } else if (cd)
       hipLaunchKernelGGL((k_cg_iter3<T, true>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, plan3<T>(G, cd).kc, stp, w.sc);
     else
       hipLaunchKernelGGL((k_cg_iter3<T, false>), dim3(w.ns), dim3(kBlock), 0, s, G, stencil<3, T>(G), it, plan3<T>(G, cd).kc, stp, w.sc);
   }
 }
 
-void cg_scalars(hipStream_t s, const Geo& G, int iter, const CgWork& w) {
-  hipLaunchKernelGGL(k_cg_scalars, dim3(1), dim3(kBlock), 0, s, w.s, w.ns, iter, w.sc);
+void cg_scalars(hipStream_t s, const Geo& G, int iter, const CgWork& w, bool cd) {
+  const CgStep st{w.s, w.ns, iter, 0, dots_apart(G, cd) ? 0 : 1};
+  hipLaunchKernelGGL(k_cg_scalars, dim3(1), dim3(kBlock), 0, s, st, w.sc);
 }
 
 template void cg_init<double>(hipStream_t, const Geo&, const CgVectors<double>&, const CgWork&, double, int);

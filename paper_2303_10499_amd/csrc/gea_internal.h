@@ -228,6 +228,7 @@ struct CgWork {
 // workgroups of the CG iteration kernel in precision T (cd: CgVectors::D null)
 template <typename T>
 int iter_grid(const Geo& G, bool cd = false);
+long iter_partials(const Geo& G);  // doubles of CgWork::s
 template <typename T>
 void cg_init(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgWork& w, double tol,
              int max_iter);
@@ -241,7 +242,7 @@ void cg_init(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgWork& w
 template <typename T>
 void cg_iter_kernel(hipStream_t s, const Geo& G, const CgVectors<T>& v, int iter, const CgWork& w,
                     bool fold);
-void cg_scalars(hipStream_t s, const Geo& G, int iter, const CgWork& w);
+void cg_scalars(hipStream_t s, const Geo& G, int iter, const CgWork& w, bool cd = false);
 bool cg_folds(const CgWork& w);
 // ---- one-launch solves (gea_cgp.hip) -----------------------------------------
 // A whole solve set up as for cg_iter_kernel (residual in v.r, initial x,
