@@ -32,7 +32,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kMT = 2;  // 16-cell M tiles per wave in the convolution
 
 __device__ __forceinline__ bf16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -83,71 +82,69 @@ __device__ __forceinline__ void coords(const CnnDims& d, int p, int& i, int& j, 
   }
 }
 
-// MODE 0: +bias, ReLU, bf16 out; 1: +bias, FP32 out (first ycount channels);
-// 2: no bias, FP32 out (backward-data).
-template <int NDIM, int CIN, int COUT, int MODE>
-__global__ __launch_bounds__(256) void k_conv(CnnDims d, const bf16_t* __restrict__ X,
-                                              const bf16_t* __restrict__ W,
-                                              const float* __restrict__ bias, void* __restrict__ Y,
-                                              int ystride, int ycount) {
+// the bf16 gradient behind a ReLU whose output was y
+__device__ __forceinline__ bf16_t masked(float dy, bf16_t y) { return f2bf(bf2f(y) > 0.f ? dy : 0.f); }
+
+// Backward data: Y (FP32, the first ycount of COUT channels) = conv(X, W).  A
+// workgroup is one wave and takes 16 cells and NTW of the output channel tiles
+// (blockIdx.y: which); it walks the K chunks in order, one chain of MFMAs, with
+// the operands of U chunks in flight: every load is made, from an index clamped
+// into the grid, and the zero padding is a select.  Bound by the latency of
+// that chain.  On a 32^3 crop the layers took 10-36 us with 32 cells and all
+// channels a wave and a branch around every load, and take 6-14 now.  (The chunks split
+// over four waves and their sums added would be another order of a sum that is
+// rounded to bf16.)
+// With act given the result leaves as the next layer's masked bf16 gradient Q
+// (see masked) instead.
+template <int NDIM, int CIN, int COUT, int NTW>
+__global__ __launch_bounds__(64) void k_conv_bwd(CnnDims d, const bf16_t* __restrict__ X,
+                                                 const bf16_t* __restrict__ W, float* __restrict__ Y,
+                                                 int ycount, const bf16_t* __restrict__ act,
+                                                 bf16_t* __restrict__ Q) {
   constexpr int NT = Taps<NDIM>::n;
   constexpr int KC = (NT * CIN + 31) / 32;
   constexpr int KPAD = KC * 32;
-  constexpr int NTILE = COUT / 16;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = lane >> 4, r = lane & 15;
-  const int pbase = (blockIdx.x * 4 + wave) * (16 * kMT);
-  int pi[kMT], pj[kMT], pk[kMT];
-  bool pv[kMT];
+  constexpr int U = NTW > 3 ? 3 : (NTW > 1 ? 4 : 9);  // chunks in flight
+  const int lane = threadIdx.x, g = lane >> 4, r = lane & 15;
+  const int pbase = blockIdx.x * 16, n0 = blockIdx.y * NTW;
+  const bool pv = pbase + r < d.npix;
+  int pi, pj, pk;
+  coords<NDIM>(d, pv ? pbase + r : 0, pi, pj, pk);
+  f32x4 acc[NTW];
 #pragma unroll
-  for (int mt = 0; mt < kMT; ++mt) {
-    const int p = pbase + mt * 16 + r;
-    pv[mt] = p < d.npix;
-    coords<NDIM>(d, pv[mt] ? p : 0, pi[mt], pj[mt], pk[mt]);
-  }
-  f32x4 acc[kMT][NTILE];
+  for (int nt = 0; nt < NTW; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int cb = 0; cb < KC; cb += U) {
+    bf16x8 bw[U][NTW], av[U];
 #pragma unroll
-  for (int mt = 0; mt < kMT; ++mt)
+    for (int u = 0; u < U; ++u) {
+      const int kc = min(cb + u, KC - 1), k = kc * 32 + 8 * g;
+      const int t = min(k / CIN, NT - 1), ci = k % CIN;
 #pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int kc = 0; kc < KC; ++kc) {
-    const int k = kc * 32 + 8 * g;
-    const int t = k / CIN, ci = k % CIN;
-    bf16x8 bw[NTILE];
+      for (int nt = 0; nt < NTW; ++nt) bw[u][nt] = load8(W + (size_t)((n0 + nt) * 16 + r) * KPAD + k);
+      const int q = neighbor<NDIM>(d, pi, pj, pk, t);
+      const bf16x8 a = load8(X + (size_t)(q < 0 ? 0 : q) * CIN + ci);
+      av[u] = k < NT * CIN && pv && q >= 0 ? a : zero8();
+    }
 #pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt)
-      bw[nt] = (t < NT) ? load8(W + (size_t)(nt * 16 + r) * KPAD + k) : zero8();
+    for (int u = 0; u < U; ++u) {
+      if (cb + u >= KC) break;
 #pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) {
-      bf16x8 a = zero8();
-      if (t < NT && pv[mt]) {
-        const int q = neighbor<NDIM>(d, pi[mt], pj[mt], pk[mt], t);
-        if (q >= 0) a = load8(X + (size_t)q * CIN + ci);
-      }
-#pragma unroll
-      for (int nt = 0; nt < NTILE; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bw[nt], acc[mt][nt], 0, 0, 0);
+      for (int nt = 0; nt < NTW; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u], bw[u][nt], acc[nt], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int mt = 0; mt < kMT; ++mt)
+  for (int nt = 0; nt < NTW; ++nt)
 #pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int p = pbase + mt * 16 + 4 * g + i;
-        const int co = nt * 16 + r;
-        if (p < d.npix && co < ycount) {
-          float v = acc[mt][nt][i];
-          if (MODE < 2) v += bias[co];
-          if (MODE == 0) {
-            v = fmaxf(v, 0.f);
-            reinterpret_cast<bf16_t*>(Y)[(size_t)p * ystride + co] = f2bf(v);
-          } else {
-            reinterpret_cast<float*>(Y)[(size_t)p * ystride + co] = v;
-          }
-        }
-      }
+    for (int i = 0; i < 4; ++i) {
+      const int p = pbase + 4 * g + i, co = (n0 + nt) * 16 + r;
+      if (p >= d.npix || co >= ycount) continue;
+      const size_t e = (size_t)p * ycount + co;
+      if (act)
+        Q[e] = masked(acc[nt][i], act[e]);
+      else
+        Y[e] = acc[nt][i];
+    }
 }
 
 // Output tile of the forward convolution: TX x TY x TZ cells, staged with a
@@ -594,9 +591,9 @@ int conv_tiles(const CnnDims& d) {
 // transposing LDS read gives, and a tap is only an offset of its address.
 // FP32 accumulators over the split, one partial per split; the bias gradient
 // sums the dY tile that is there already.  On 32^3 cells the latency of one
-// tile's load and of its eight chunks bounds it: 10-14 us a layer, where
-// gathering every operand element by element from global memory took 36-85
-// (and a pass of its own over dY for the bias 20).
+// tile's load and of its eight chunks bounds it: 10-14 us for a layer alone,
+// where gathering every operand element by element from global memory took
+// 36-85 (and a pass of its own over dY for the bias 20).
 template <int NDIM>
 struct WgradTile {
   static constexpr int TX = 8, TY = NDIM == 3 ? 8 : 1, TZ = NDIM == 3 ? 4 : 32;
@@ -607,8 +604,8 @@ struct WgradTile {
   static constexpr int XB = SX * HY * HZ * 32;             // bytes of them
 };
 
-// Splits of the cells: as many as give three workgroups a CU over the input
-// channel tiles, at most one per cell tile.
+// Splits of the cells: as many as give a workgroup a CU over the input channel
+// tiles (all layers run together), at most one per cell tile.
 struct WgradPlan {
   int tiles, per, nsplit;  // cell tiles, tiles per split, splits
 };
@@ -617,7 +614,7 @@ WgradPlan wgrad_plan(const CnnDims& d, int ndim, int cin_p) {
   const int tyz = ndim == 3 ? ((d.ny + 7) / 8) * ((d.nz + 3) / 4) : (d.nz + 31) / 32;
   WgradPlan w;
   w.tiles = tx * tyz;
-  const int want = 3 * kCus / ((cin_p + 15) / 16);
+  const int want = kCus / ((cin_p + 15) / 16);
   const int n = w.tiles < want ? w.tiles : want;
   w.per = (w.tiles + n - 1) / n;
   w.nsplit = (w.tiles + w.per - 1) / w.per;
@@ -636,10 +633,32 @@ __device__ __forceinline__ uint4 cells8(const unsigned char* lo, int stride4) {
   return make_uint4(a.x, a.y, b.x, b.y);
 }
 
+// one layer's gradient in a launch: its grid, operands and partials, and its
+// workgroups [block0, block0 + nci * nsplit)
+struct WgradJob {
+  CnnDims d;
+  WgradPlan w;
+  const bf16_t *X, *dY;
+  float* part;
+  double* bpart;
+  int block0, nci;
+  // the reduction
+  int red0, cin, cin_p, cout, cout_p, kpad;
+  long woff;
+};
+struct WgradJobs {
+  WgradJob l[kCnnLayers];
+};
+constexpr int kWgradOrder[kCnnLayers] = {2, 3, 1, 4, 5, 0};  // (the longest workgroups first)
+
 template <int NDIM, int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_wgrad(CnnDims d, WgradPlan w, const bf16_t* __restrict__ X,
-                                               const bf16_t* __restrict__ dY,
-                                               float* __restrict__ part, double* __restrict__ bpart) {
+__device__ __forceinline__ void wgrad_layer(const WgradJob& job, int block, unsigned char* sX, unsigned char* sD) {
+  const CnnDims& d = job.d;
+  const WgradPlan& w = job.w;
+  const bf16_t* const X = job.X;
+  const bf16_t* const dY = job.dY;
+  float* const part = job.part;
+  double* const bpart = job.bpart;
   using T = WgradTile<NDIM>;
   constexpr int NT = Taps<NDIM>::n;
   constexpr int KPAD = (NT * CIN + 31) / 32 * 32;
@@ -647,12 +666,10 @@ __global__ __launch_bounds__(256) void k_wgrad(CnnDims d, WgradPlan w, const bf1
   constexpr int TW = (NT + 3) / 4;             // taps per wave
   constexpr int XH = CIN < 16 ? 1 : 2;         // 16-byte units per staged cell
   constexpr int DU = T::CELLS * COUT / 8;      // 16-byte units of the dY tile
-  __shared__ __attribute__((aligned(16))) unsigned char sX[T::XB];
-  __shared__ __attribute__((aligned(16))) unsigned char sD[T::CELLS * COUT * 2];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, r = lane & 15;
-  const int ci0 = blockIdx.x * 16;
-  const int split = blockIdx.y;
+  const int ci0 = block % job.nci * 16;
+  const int split = block / job.nci;
   const int ntx = (d.nx + T::TX - 1) / T::TX;
   const int nty = NDIM == 3 ? (d.ny + T::TY - 1) / T::TY : 1;
   f32x4 acc[TW][MTI];
@@ -727,7 +744,7 @@ __global__ __launch_bounds__(256) void k_wgrad(CnnDims d, WgradPlan w, const bf1
           acc[u][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], __builtin_bit_cast(bf16x8, b), acc[u][mt], 0, 0, 0);
       }
     }
-    if (blockIdx.x == 0) {  // the bias gradient's share, in FP64: thread = (cell group, channel)
+    if (ci0 == 0) {  // the bias gradient's share, in FP64: thread = (cell group, channel)
       const bf16_t* sd = reinterpret_cast<const bf16_t*>(sD);
 #pragma unroll 8
       for (int q = threadIdx.x / COUT; q < T::CELLS; q += 256 / COUT)
@@ -744,7 +761,7 @@ __global__ __launch_bounds__(256) void k_wgrad(CnnDims d, WgradPlan w, const bf1
       for (int i = 0; i < 4; ++i)
         part[((size_t)split * COUT + mt * 16 + 4 * g + i) * KPAD + t * CIN + ci0 + r] = acc[u][mt][i];
   }
-  if (blockIdx.x == 0) {
+  if (ci0 == 0) {
     double* sb = reinterpret_cast<double*>(sX);
     __syncthreads();
     sb[threadIdx.x] = bsum;
@@ -757,19 +774,48 @@ __global__ __launch_bounds__(256) void k_wgrad(CnnDims d, WgradPlan w, const bf1
   }
 }
 
+// the weight gradients of all layers in one launch (their operands are all
+// there once the data gradients are): on a 32^3 crop 29 us where the six
+// launches took 74, none of which filled the card
+template <int NDIM>
+__global__ __launch_bounds__(256) void k_wgrad(WgradJobs jobs) {
+  using T = WgradTile<NDIM>;
+  __shared__ __attribute__((aligned(16))) unsigned char sX[T::XB];
+  __shared__ __attribute__((aligned(16))) unsigned char sD[T::CELLS * 64 * 2];
+  const int b = blockIdx.x;
+  if (b >= jobs.l[0].block0)
+    wgrad_layer<NDIM, 8, 16>(jobs.l[0], b - jobs.l[0].block0, sX, sD);
+  else if (b >= jobs.l[5].block0)
+    wgrad_layer<NDIM, 16, 16>(jobs.l[5], b - jobs.l[5].block0, sX, sD);
+  else if (b >= jobs.l[4].block0)
+    wgrad_layer<NDIM, 48, 16>(jobs.l[4], b - jobs.l[4].block0, sX, sD);
+  else if (b >= jobs.l[1].block0)
+    wgrad_layer<NDIM, 16, 32>(jobs.l[1], b - jobs.l[1].block0, sX, sD);
+  else if (b >= jobs.l[3].block0)
+    wgrad_layer<NDIM, 96, 32>(jobs.l[3], b - jobs.l[3].block0, sX, sD);
+  else
+    wgrad_layer<NDIM, 32, 64>(jobs.l[2], b - jobs.l[2].block0, sX, sD);
+}
+
 // Sum the weight- and bias-gradient partials over the splits into the packed
 // gradient (logical layout W[co][tap][ci], then b[co]), in FP64: 16 threads
 // share an element, so that few elements over many splits fill the chip too
-// (4-6 us a layer on 32^3 cells; one thread an element took 16).
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part,
-                                                      const double* __restrict__ bpart, int nsplit,
-                                                      int cout_p, int kpad, int cin, int cin_p,
-                                                      int cout, int ntaps, float* __restrict__ gW,
+// (all layers in one launch 13 us on 32^3 cells; one thread an element took 16
+// a layer).
+__global__ __launch_bounds__(256) void k_wgrad_reduce(WgradJobs jobs, int ntaps, float* __restrict__ grad,
                                                       int accumulate) {
   __shared__ double sh[16][17];
+  int l = 0;  // (the layers' blocks lie in layer order)
+  while (l + 1 < kCnnLayers && (int)blockIdx.x >= jobs.l[l + 1].red0) ++l;
+  const WgradJob& job = jobs.l[l];
+  const float* const part = job.part;
+  const double* const bpart = job.bpart;
+  float* const gW = grad + job.woff;
+  const int nsplit = job.w.nsplit, cout_p = job.cout_p, kpad = job.kpad, cin = job.cin, cin_p = job.cin_p,
+            cout = job.cout;
   const int nW = cout * ntaps * cin, total = nW + cout;
   const int le = threadIdx.x & 15, ls = threadIdx.x >> 4;
-  const int e = blockIdx.x * 16 + le;
+  const int e = ((int)blockIdx.x - job.red0) * 16 + le;
   double s = 0.0;
   if (e < nW) {
     const int ci = e % cin, t = (e / cin) % ntaps, co = e / (cin * ntaps);
@@ -831,27 +877,13 @@ __global__ __launch_bounds__(256) void k_upcat(CnnDims d, int CA, int CB,
   }
 }
 
-// out = bf16(dy * (y > 0)) (mask = 0: no mask); C channels, padded to Cp in out
-__global__ __launch_bounds__(256) void k_mask(int npix, int C, int Cp, const float* __restrict__ dy,
-                                              const bf16_t* __restrict__ y, int mask,
-                                              bf16_t* __restrict__ out) {
-  const long total = (long)npix * Cp;
-  for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
-    const int c = (int)(e % Cp), p = (int)(e / Cp);
-    float v = 0.f;
-    if (c < C) {
-      v = dy[(size_t)p * C + c];
-      if (mask && !(bf2f(y[(size_t)p * C + c]) > 0.f)) v = 0.f;
-    }
-    out[e] = f2bf(v);
-  }
-}
-
-// dA[q] = sum over the fine children of dcat[child][0:CA]; dB[p] = dcat[p][CA:]
+// qA[q] = the masked gradient of A: sum over the fine children of
+// dcat[child][0:CA]; dB[p] = dcat[p][CA:]
 template <int NDIM>
 __global__ __launch_bounds__(256) void k_upcat_bwd(CnnDims dc, int CA, int CB,
                                                    const float* __restrict__ dcat,
-                                                   float* __restrict__ dA, float* __restrict__ dB) {
+                                                   const bf16_t* __restrict__ A, bf16_t* __restrict__ qA,
+                                                   float* __restrict__ dB) {
   const int C = CA + CB;
   const int nxf = 2 * dc.nx, nyf = NDIM == 3 ? 2 * dc.ny : 1;
   const long tA = (long)dc.npix * CA;
@@ -866,7 +898,7 @@ __global__ __launch_bounds__(256) void k_upcat_bwd(CnnDims dc, int CA, int CB,
           const int p = (2 * i + dx) + nxf * ((NDIM == 3 ? 2 * j + dy : 0) + nyf * (2 * k + dz));
           s += dcat[(size_t)p * C + c];
         }
-    dA[e] = s;
+    qA[e] = masked(s, A[e]);
   }
   const long nfine = (long)dc.npix * (NDIM == 3 ? 8 : 4);
   const long tB = nfine * CB;
@@ -876,10 +908,11 @@ __global__ __launch_bounds__(256) void k_upcat_bwd(CnnDims dc, int CA, int CB,
   }
 }
 
-// dE[p] += dP[parent(p)] / 2^ndim on the fine grid d
+// qE[p] = the masked sum of dE[p] and dP[parent(p)] / 2^ndim on the fine grid d
 template <int NDIM>
 __global__ __launch_bounds__(256) void k_pool_bwd_add(CnnDims d, int C, const float* __restrict__ dP,
-                                                      float* __restrict__ dE) {
+                                                      const float* __restrict__ dE,
+                                                      const bf16_t* __restrict__ E, bf16_t* __restrict__ qE) {
   const int nxc = d.nx / 2, nyc = NDIM == 3 ? d.ny / 2 : 1;
   const long total = (long)d.npix * C;
   for (long e = blockIdx.x * (long)blockDim.x + threadIdx.x; e < total; e += (long)gridDim.x * blockDim.x) {
@@ -887,19 +920,23 @@ __global__ __launch_bounds__(256) void k_pool_bwd_add(CnnDims d, int C, const fl
     int i, j, k;
     coords<NDIM>(d, p, i, j, k);
     const int q = (i / 2) + nxc * ((NDIM == 3 ? j / 2 : 0) + nyc * (k / 2));
-    dE[e] += dP[(size_t)q * C + c] * (NDIM == 3 ? 0.125f : 0.25f);
+    float v = dE[e];
+    v += dP[(size_t)q * C + c] * (NDIM == 3 ? 0.125f : 0.25f);
+    qE[e] = masked(v, E[e]);
   }
 }
 
-// dY[p] = (y - t)/npix in channel 0 of 16; loss partials sum (y - t)^2
+// q5[p] = bf16 (y - t)/npix in channel 0 of 16; loss partials sum (y - t)^2
 __global__ __launch_bounds__(256) void k_loss(int npix, const float* __restrict__ y,
-                                              const float* __restrict__ t, float* __restrict__ dY,
+                                              const float* __restrict__ t, bf16_t* __restrict__ q5,
                                               double* __restrict__ lpart) {
   __shared__ double sh[1][kBlock / 64];
   double a[1] = {0.0};
   for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < npix; p += gridDim.x * blockDim.x) {
     const float e = y[p] - t[p];
-    dY[p] = e / (float)npix;
+    uint4* const o = reinterpret_cast<uint4*>(q5 + (size_t)p * 16);
+    o[0] = make_uint4((uint32_t)f2bf(e / (float)npix), 0u, 0u, 0u);
+    o[1] = make_uint4(0u, 0u, 0u, 0u);
     a[0] += (double)e * (double)e;
   }
   Reducer<0u, 1>::block(a, sh);
@@ -1423,7 +1460,6 @@ __global__ __launch_bounds__(256) void k_packz(const float* __restrict__ mW, int
   }
 }
 
-int conv_blocks(int npix) { return (npix + 4 * 16 * kMT - 1) / (4 * 16 * kMT); }
 
 // ---- dispatch -------------------------------------------------------------------
 
@@ -1493,14 +1529,25 @@ void conv_fwd(const Cnn& n, int layer, const bf16_t* X, const bf16_t* A, void* Y
 
 // dX (FP32, cin channels) = conv(dYmasked (bf16, cout_p channels), Wt)
 template <int NDIM>
-void conv_bwd_data(const Cnn& n, int layer, const bf16_t* dYq, float* dX) {
+void conv_bwd_data(const Cnn& n, int layer, const bf16_t* dYq, float* dX, const bf16_t* act = nullptr,
+                   bf16_t* q = nullptr) {
   const CnnLayer& L = n.L[layer];
   const CnnDims& d = n.d[L.level];
-  const dim3 gr(conv_blocks(d.npix)), bl(256);
+  const dim3 bl(64);
   hipStream_t s = n.s;
-#define GEA_CONVT(CI, CO, YS)                                                                   \
-  hipLaunchKernelGGL((k_conv<NDIM, CI, CO, 2>), gr, bl, 0, s, d, dYq, n.Wt[layer],            \
-                     (const float*)nullptr, (void*)dX, YS, YS)
+  // one channel tile a wave until that gives four waves a SIMD, then all: the
+  // cells' operands are then read once
+  const bool all = d.npix >= 16 * 16 * kCus / (L.cin_t_p / 16);
+#define GEA_CONVT(CI, CO, YS)                                                                       \
+  do {                                                                                              \
+    const int nb = (d.npix + 15) / 16;                                                              \
+    if (all)                                                                                        \
+      hipLaunchKernelGGL((k_conv_bwd<NDIM, CI, CO, CO / 16>), dim3(nb), bl, 0, s, d, dYq,           \
+                         n.Wt[layer], dX, YS, act, q);                                                      \
+    else                                                                                            \
+      hipLaunchKernelGGL((k_conv_bwd<NDIM, CI, CO, 1>), dim3(nb, CO / 16), bl, 0, s, d, dYq,        \
+                         n.Wt[layer], dX, YS, act, q);                                                      \
+  } while (0)
   switch (layer) {
     case 1: GEA_CONVT(32, 16, 16); break;
     case 2: GEA_CONVT(64, 32, 32); break;
@@ -1511,29 +1558,39 @@ void conv_bwd_data(const Cnn& n, int layer, const bf16_t* dYq, float* dX) {
 #undef GEA_CONVT
 }
 
+// the weight and bias gradients of all layers, behind the data gradients
 template <int NDIM>
-void conv_wgrad(const Cnn& n, int layer, const bf16_t* X, const bf16_t* dYq, bool acc) {
-  const CnnLayer& L = n.L[layer];
-  const CnnDims& d = n.d[L.level];
-  const WgradPlan w = wgrad_plan(d, NDIM, L.cin_p);
-  const dim3 gr((L.cin_p + 15) / 16, w.nsplit), bl(256);
-  hipStream_t s = n.s;
-#define GEA_WG(CI, CO) \
-  hipLaunchKernelGGL((k_wgrad<NDIM, CI, CO>), gr, bl, 0, s, d, w, X, dYq, n.part, n.bpart)
-  switch (layer) {
-    case 0: GEA_WG(8, 16); break;
-    case 1: GEA_WG(16, 32); break;
-    case 2: GEA_WG(32, 64); break;
-    case 3: GEA_WG(96, 32); break;
-    case 4: GEA_WG(48, 16); break;
-    case 5: GEA_WG(16, 16); break;
-  }
-#undef GEA_WG
+void weight_gradients(const Cnn& n, bool acc) {
+  const bf16_t* const X[kCnnLayers] = {n.xin, n.p0, n.p1, n.c1, n.c0, n.d0};
+  const bf16_t* const q[kCnnLayers] = {n.q0, n.q1, n.q2, n.q3, n.q4, n.q5};
   const int ntaps = NDIM == 2 ? 9 : 27;
-  const int nout = L.cout * ntaps * L.cin + L.cout;  // the bias follows the weights
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((nout + 15) / 16), bl, 0, s, (const float*)n.part,
-                     (const double*)n.bpart, w.nsplit, L.cout_p, L.kpad, L.cin, L.cin_p, L.cout,
-                     ntaps, n.grad + L.woff, (int)acc);
+  WgradJobs jobs;
+  int blocks = 0, red = 0;
+  for (int l = 0; l < kCnnLayers; ++l) {
+    const CnnLayer& L = n.L[l];
+    WgradJob& j = jobs.l[l];
+    j.d = n.d[L.level];
+    j.w = wgrad_plan(j.d, NDIM, L.cin_p);
+    j.X = X[l];
+    j.dY = q[l];
+    j.part = n.part[l];
+    j.bpart = n.bpart[l];
+    j.nci = (L.cin_p + 15) / 16;
+    j.cin = L.cin;
+    j.cin_p = L.cin_p;
+    j.cout = L.cout;
+    j.cout_p = L.cout_p;
+    j.kpad = L.kpad;
+    j.woff = L.woff;
+    j.red0 = red;
+    red += (L.cout * ntaps * L.cin + L.cout + 15) / 16;  // (the bias follows the weights)
+  }
+  for (int l : kWgradOrder) {
+    jobs.l[l].block0 = blocks;
+    blocks += jobs.l[l].nci * jobs.l[l].w.nsplit;
+  }
+  hipLaunchKernelGGL(k_wgrad<NDIM>, dim3(blocks), dim3(256), 0, n.s, jobs);
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(red), dim3(256), 0, n.s, jobs, ntaps, n.grad, (int)acc);
 }
 
 // the forward convolution of one layer on the network's own buffers
@@ -1580,35 +1637,20 @@ template <int NDIM>
 void backward_t(Cnn& n, bool acc) {
   hipStream_t s = n.s;
   const dim3 bl(256);
-  const int N0 = n.d[0].npix, N1 = n.d[1].npix, N2 = n.d[2].npix;
-  hipLaunchKernelGGL(k_loss, dim3(cnn_loss_partials(n)), bl, 0, s, N0, (const float*)n.y, (const float*)n.t, n.dy5, n.lpart);
+  const int N0 = n.d[0].npix, N1 = n.d[1].npix;
   // layer 5 (no ReLU): dY5 has one channel, padded to 16 for the MFMA kernels
-  hipLaunchKernelGGL(k_mask, dim3(blocks_for((long)N0 * 16)), bl, 0, s, N0, 1, 16, (const float*)n.dy5, (const bf16_t*)nullptr, 0, n.q5);
-  conv_wgrad<NDIM>(n, 5, n.d0, n.q5, acc);
-  conv_bwd_data<NDIM>(n, 5, n.q5, n.dd0);
-  // layer 4
-  hipLaunchKernelGGL(k_mask, dim3(blocks_for((long)N0 * 16)), bl, 0, s, N0, 16, 16, (const float*)n.dd0, (const bf16_t*)n.d0, 1, n.q4);
-  conv_wgrad<NDIM>(n, 4, n.c0, n.q4, acc);
+  hipLaunchKernelGGL(k_loss, dim3(cnn_loss_partials(n)), bl, 0, s, N0, (const float*)n.y, (const float*)n.t, n.q5, n.lpart);
+  conv_bwd_data<NDIM>(n, 5, n.q5, nullptr, n.d0, n.q4);
   conv_bwd_data<NDIM>(n, 4, n.q4, n.dc0);
-  hipLaunchKernelGGL(k_upcat_bwd<NDIM>, dim3(blocks_for((long)N0 * 16)), bl, 0, s, n.d[1], 32, 16, (const float*)n.dc0, n.dd1, n.de0);
-  // layer 3
-  hipLaunchKernelGGL(k_mask, dim3(blocks_for((long)N1 * 32)), bl, 0, s, N1, 32, 32, (const float*)n.dd1, (const bf16_t*)n.d1, 1, n.q3);
-  conv_wgrad<NDIM>(n, 3, n.c1, n.q3, acc);
+  hipLaunchKernelGGL(k_upcat_bwd<NDIM>, dim3(blocks_for((long)N0 * 16)), bl, 0, s, n.d[1], 32, 16, (const float*)n.dc0, (const bf16_t*)n.d1, n.q3, n.de0);
   conv_bwd_data<NDIM>(n, 3, n.q3, n.dc1);
-  hipLaunchKernelGGL(k_upcat_bwd<NDIM>, dim3(blocks_for((long)N1 * 32)), bl, 0, s, n.d[2], 64, 32, (const float*)n.dc1, n.de2, n.de1);
-  // layer 2
-  hipLaunchKernelGGL(k_mask, dim3(blocks_for((long)N2 * 64)), bl, 0, s, N2, 64, 64, (const float*)n.de2, (const bf16_t*)n.e2, 1, n.q2);
-  conv_wgrad<NDIM>(n, 2, n.p1, n.q2, acc);
+  hipLaunchKernelGGL(k_upcat_bwd<NDIM>, dim3(blocks_for((long)N1 * 32)), bl, 0, s, n.d[2], 64, 32, (const float*)n.dc1, (const bf16_t*)n.e2, n.q2, n.de1);
   conv_bwd_data<NDIM>(n, 2, n.q2, n.dp1);
-  hipLaunchKernelGGL(k_pool_bwd_add<NDIM>, dim3(blocks_for((long)N1 * 32)), bl, 0, s, n.d[1], 32, (const float*)n.dp1, n.de1);
-  // layer 1
-  hipLaunchKernelGGL(k_mask, dim3(blocks_for((long)N1 * 32)), bl, 0, s, N1, 32, 32, (const float*)n.de1, (const bf16_t*)n.e1, 1, n.q1);
-  conv_wgrad<NDIM>(n, 1, n.p0, n.q1, acc);
+  hipLaunchKernelGGL(k_pool_bwd_add<NDIM>, dim3(blocks_for((long)N1 * 32)), bl, 0, s, n.d[1], 32, (const float*)n.dp1, (const float*)n.de1, (const bf16_t*)n.e1, n.q1);
   conv_bwd_data<NDIM>(n, 1, n.q1, n.dp0);
-  hipLaunchKernelGGL(k_pool_bwd_add<NDIM>, dim3(blocks_for((long)N0 * 16)), bl, 0, s, n.d[0], 16, (const float*)n.dp0, n.de0);
-  // layer 0 (no input gradient needed)
-  hipLaunchKernelGGL(k_mask, dim3(blocks_for((long)N0 * 16)), bl, 0, s, N0, 16, 16, (const float*)n.de0, (const bf16_t*)n.e0, 1, n.q0);
-  conv_wgrad<NDIM>(n, 0, n.xin, n.q0, acc);
+  hipLaunchKernelGGL(k_pool_bwd_add<NDIM>, dim3(blocks_for((long)N0 * 16)), bl, 0, s, n.d[0], 16, (const float*)n.dp0, (const float*)n.de0, (const bf16_t*)n.e0, n.q0);
+  // (layer 0 needs no input gradient)
+  weight_gradients<NDIM>(n, acc);
 }
 
 }  // namespace
@@ -1710,13 +1752,9 @@ size_t cnn_carve(Cnn& n, int ndim, int nx, int ny, int nz, bool train, char* bas
     n.m = (float*)take(n.nparams * F4);
     n.v = (float*)take(n.nparams * F4);
     n.t = (float*)take(N0 * F4);
-    n.dy5 = (float*)take(N0 * F4);
-    n.dd0 = (float*)take(N0 * 16 * F4);
     n.dc0 = (float*)take(N0 * 48 * F4);
-    n.dd1 = (float*)take(N1 * 32 * F4);
     n.de0 = (float*)take(N0 * 16 * F4);
     n.dc1 = (float*)take(N1 * 96 * F4);
-    n.de2 = (float*)take(N2 * 64 * F4);
     n.de1 = (float*)take(N1 * 32 * F4);
     n.dp1 = (float*)take(N2 * 32 * F4);
     n.dp0 = (float*)take(N1 * 16 * F4);
@@ -1726,16 +1764,12 @@ size_t cnn_carve(Cnn& n, int ndim, int nx, int ny, int nz, bool train, char* bas
     n.q2 = (bf16_t*)take(N2 * 64 * B2);
     n.q1 = (bf16_t*)take(N1 * 32 * B2);
     n.q0 = (bf16_t*)take(N0 * 16 * B2);
-    long mx = 0, mb = 0;
     for (int l = 0; l < kCnnLayers; ++l) {
       const CnnLayer& L = n.L[l];
-      const long ns = wgrad_plan(n.d[L.level], ndim, L.cin_p).nsplit;
-      const long need = ns * L.cout_p * L.kpad;
-      if (need > mx) mx = need;
-      if (ns * L.cout_p > mb) mb = ns * L.cout_p;
+      const size_t ns = wgrad_plan(n.d[L.level], ndim, L.cin_p).nsplit;
+      n.part[l] = (float*)take(ns * L.cout_p * L.kpad * F4);
+      n.bpart[l] = (double*)take(ns * L.cout_p * sizeof(double));
     }
-    n.part = (float*)take((size_t)mx * F4);
-    n.bpart = (double*)take((size_t)mb * sizeof(double));
     n.lpart = (double*)take(sizeof(double) * 1024);
   }
   return off;

@@ -56,10 +56,10 @@ struct Cnn {
   float* y;   // output, 1 channel
   float* xf;  // FP32 staging of the 2-channel input
   // backward
-  float *t, *dy5, *dd0, *dc0, *dd1, *de0, *dc1, *de2, *de1, *dp1, *dp0;
+  float *t, *dc0, *de0, *dc1, *de1, *dp1, *dp0;
   bf16_t *q5, *q4, *q3, *q2, *q1, *q0;  // bf16 copies of the (masked) output gradients
-  float* part;    // weight-gradient partials of the splits
-  double* bpart;  // bias-gradient partials
+  float* part[kCnnLayers];    // weight-gradient partials of the splits
+  double* bpart[kCnnLayers];  // bias-gradient partials
   double* lpart;
 };
 
