@@ -279,6 +279,17 @@ struct gea_ctx {
   // (variant 0 where the mesh takes the iteration kernels) and their exchange area
   CgpPlan plan_e{}, plan64{}, plan32{};
   uint64_t* cgx = nullptr;
+  // One-launch solves of a step whose scalars are read with the step's last
+  // read (see step_deferred): on while `defer`, off for `eager_steps` more steps
+  // once one of them did not end well
+  struct Deferred {
+    CgScalars hs;
+    int corr, sweep;  // the corrector or (corr -1) the energy sweep it solved
+  };
+  static constexpr int kMaxDeferred = 4;  // (of the eight snapshots between two reads)
+  Deferred deferred[kMaxDeferred];
+  int ndeferred = 0, eager_steps = 0;
+  bool defer = false;
   uint64_t spin = kCgpSpin;  // how long a workgroup of theirs waits (gea_set_wait_limit)
   int dev = 0;
   std::unique_lock<std::mutex> big;  // see hold_card
@@ -700,6 +711,24 @@ void cast_system(gea_ctx* x) {
   x->sys32 = true;
 }
 
+// A one-launch solve just enqueued: its scalars wait for a later read.
+bool deferred(gea_ctx* x, int corr, int sweep) {
+  if (!x->defer || x->ndeferred == gea_ctx::kMaxDeferred) return false;
+  gea_ctx::Deferred& d = x->deferred[x->ndeferred++];
+  d = gea_ctx::Deferred{CgScalars{}, corr, sweep};
+  snapshot(x, x->sc, &d.hs, sizeof d.hs);
+  return true;
+}
+
+// what an FP64 solve that ended says of itself
+void pcg64_stats(const CgScalars& hs, gea_solve_stats* out) {
+  out->rel_res0 = hs.bb > 0 ? std::sqrt(hs.rr0 / hs.bb) : 0.0;
+  out->iters = hs.iter;
+  out->outer_iters = 0;
+  out->rel_res = std::sqrt(hs.rr / hs.bb);
+  out->status = hs.status == 0 ? GEA_OK : (hs.status == -4 ? GEA_ERR_NOCONV : GEA_ERR_NAN);
+}
+
 // FP64 Jacobi-PCG on (c, D, dinv, b) from the initial guess in xv.
 gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
   const Geo& G = x->G;
@@ -709,6 +738,10 @@ gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
   if (x->plan64.variant) {
     hold_card(x, x->plan64);
     x->timer.run(0, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan64, x->cgx, x->spin, x->sc); });
+    if (deferred(x, x->corr, 0)) {
+      HIPCHK(hipGetLastError());
+      return GEA_OK;
+    }
   }
   HIPCHK(hipGetLastError());
   CgScalars hs;
@@ -732,10 +765,7 @@ gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
       });
   if (rc != GEA_OK) return rc;
   last64 = hs.iter;
-  out->iters = hs.iter;
-  out->outer_iters = 0;
-  out->rel_res = std::sqrt(hs.rr / hs.bb);
-  out->status = hs.status == 0 ? GEA_OK : (hs.status == -4 ? GEA_ERR_NOCONV : GEA_ERR_NAN);
+  pcg64_stats(hs, out);
   return (gea_status)out->status;
 }
 
@@ -1182,6 +1212,11 @@ gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters
   if (x->plan_e.variant) {
     hold_card(x, x->plan_e);
     x->timer.run(7, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan_e, x->cgx, x->spin, w.sc); });
+    if (deferred(x, -1, sweep)) {
+      HIPCHK(hipGetLastError());
+      *iters = 0;  // (counted with the read)
+      return GEA_OK;
+    }
     read_scalars(x, x->sc, &hs);
     check_cgp(x, hs);
     if (!hs.done) hs = CgScalars{};  // (b = 0)
@@ -1377,7 +1412,7 @@ gea_status steps_1_2(gea_ctx* x, const State& S, double* T_out, double* pp_out =
   return GEA_OK;
 }
 
-gea_status one_step(gea_ctx* x, gea_step_stats* stats) {
+gea_status step_once(gea_ctx* x, gea_step_stats* stats, bool* redo) {
   const Geo& G = x->G;
   const Phys& ph = x->ph;
   hipStream_t s = x->stream;
@@ -1426,6 +1461,24 @@ gea_status one_step(gea_ctx* x, gea_step_stats* stats) {
     hs = x->last_h64;
   else
     read_scalars(x, x->sc, &hs);
+  for (int k = 0; k < x->ndeferred; ++k) {
+    const gea_ctx::Deferred& d = x->deferred[k];
+    check_cgp(x, d.hs);
+    if (!d.hs.done || d.hs.status != 0 || d.hs.bb == 0.0) {
+      *redo = true;
+      return GEA_OK;
+    }
+    if (d.corr < 0) {
+      x->last_iters_energy[d.sweep < 8 ? d.sweep : 7] = d.hs.iter;
+      stats->energy_iters += d.hs.iter;
+      continue;
+    }
+    gea_solve_stats& ss = stats->solve[d.corr];
+    pcg64_stats(d.hs, &ss);
+    x->last_iters64[d.corr < 8 ? d.corr : 7] = d.hs.iter;
+    stats->total_iters += ss.iters;
+    if (ss.rel_res > stats->max_rel_res) stats->max_rel_res = ss.rel_res;
+  }
   stats->mass = hs.aux[0];
   stats->eos_mismatch = hs.aux[1];
   if (hs.aux[2] != 0.0) return GEA_ERR_NAN;
@@ -1434,6 +1487,50 @@ gea_status one_step(gea_ctx* x, gea_step_stats* stats) {
   x->cur = 1 - x->cur;
   stats->steps_done += 1;
   return GEA_OK;
+}
+
+// One step.  Its one-launch solves decide on the device when they end, and the
+// step's kernels need no host decision between them, so their scalars are
+// read with the last read of the step: on 64 x 32 cells four waits of the host
+// a step became one, and the step went from 280 to 200 us.  A step in which such a solve did not
+// end well (no convergence, a non-finite value, b = 0) has written the other
+// state only: it is done again with a read behind each solve, whose outcome
+// counts, as are the steps after it for a while.
+gea_status step_deferred(gea_ctx* x, gea_step_stats* stats) {
+  const gea_step_stats before = *stats;
+  bool redo = false;
+  x->ndeferred = 0;
+  if (x->eager_steps > 0) {
+    --x->eager_steps;
+    return step_once(x, stats, &redo);
+  }
+  struct Off {
+    gea_ctx* x;
+    ~Off() { x->defer = false; }
+  } off{x};
+  x->defer = true;
+  const gea_status rc = step_once(x, stats, &redo);
+  if (!redo && (rc == GEA_OK || x->ndeferred == 0)) return rc;
+  x->defer = false;
+  HIPCHK(hipStreamSynchronize(x->stream));
+  if (x->big.owns_lock()) x->big.unlock();
+  x->nsnap = 0;
+  x->ndeferred = 0;
+  x->tail = nullptr;
+  x->res_parts = 0;
+  x->eager_steps = 16;
+  *stats = before;
+  return step_once(x, stats, &redo);
+}
+
+gea_status one_step(gea_ctx* x, gea_step_stats* stats) {
+  const gea_step_stats before = *stats;
+  try {
+    return step_deferred(x, stats);
+  } catch (const CgpAborted&) {  // (the step is done again: counted once)
+    *stats = before;
+    throw;
+  }
 }
 
 gea_status fail(gea_ctx* x, gea_status st, const std::string& msg) {
