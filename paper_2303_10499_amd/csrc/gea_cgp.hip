@@ -201,8 +201,10 @@ __device__ __forceinline__ bool sums_of_all(const double (&sh_w)[8][8], double (
 // what a solve leaves (one thread a workgroup)
 __device__ __forceinline__ void leave_scalars(CgScalars* sc, uint64_t* ex, int status, int iter,
                                               double rr, bool bad, bool corrects, uint32_t base) {
-  if (status == kCgpAborted) {  // (any workgroup may be the one that waited too long)
-    __hip_atomic_store(&sc->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // Any workgroup may be the one that waited too long, and workgroup 0 may end
+  // well beside it: of the two the lesser status, given up, stays.
+  if (status == kCgpAborted) {
+    __hip_atomic_fetch_min(&sc->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else if (blockIdx.x == 0) {
     sc->iter = iter + 1;
@@ -210,7 +212,7 @@ __device__ __forceinline__ void leave_scalars(CgScalars* sc, uint64_t* ex, int s
     sc->fin = bad ? 0 : 1;
     sc->done_iter = iter + 1;
     if (corrects && !bad) sc->corrected = 1;
-    sc->status = status;
+    __hip_atomic_fetch_min(&sc->status, status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&sc->done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     word_store(ex, 0u, base + 1u + (uint32_t)iter);
   }
