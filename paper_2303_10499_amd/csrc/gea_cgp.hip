@@ -261,13 +261,16 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
     dg += k > 0 ? wz0 : T(0);
     return T(1) / dg;
   };
-  auto weight = [&](T a, T b, T k) { return T(0.5) * (a + b) * k; };
+  // (half the constant: the same bits as 0.5 (a + b) k, a product less: 2048^2
+  // FP32 steps 9.07 to 8.92 ms)
+  const T hx = T(0.5) * kx, hz = T(0.5) * kz;
+  auto weight = [](T a, T b, T half_k) { return (a + b) * half_k; };
 
   // ---- the tile's vectors: cells outside the mesh hold zeros throughout
   T r[R], q[R], p[R], m[R];
   T x[XL ? 1 : R], c[XL ? 1 : R];
   T d[CD ? 1 : R + 1], wd0 = T(0);  // D of the rows and the one above; weight of row 0's lower face
-  const T kxr = i + 1 < nx ? kx : T(0);  // (no face on the wall)
+  const T kxr = i + 1 < nx ? hx : T(0);  // (no face on the wall)
   const T wrc = CD && in && i + 1 < nx ? wx0 : T(0), wlc = CD && in && i > 0 ? wx0 : T(0);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -292,7 +295,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
       d[j] = v.D[P];
       if (j == 0) {
         const T dd = v.D[ok && k > 0 ? P - nx : P];
-        wd0 = ok && k > 0 ? weight(dd, d[0], kz) : T(0);
+        wd0 = ok && k > 0 ? weight(dd, d[0], hz) : T(0);
       }
       if (j == R - 1) d[R] = v.D[k + 1 < nz ? P + nx : P];
     }
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
       const int k = k0 + lane, il = bx * W + sx * 64;
       if (il > 0 && il < nx && k < nz) {
         const int P = il + nx * k;
-        wl_edge[w][lane] = weight(v.D[P - 1], v.D[P], kx);
+        wl_edge[w][lane] = weight(v.D[P - 1], v.D[P], hx);
       }
       if (il + 64 < nx && k < nz) dr_edge[w][lane] = v.D[il + 64 + nx * k];
     }
@@ -398,7 +401,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
         asm volatile("" : "+v"(d[j]));
         wrj = weight(d[j], lane_next<true>(dr_edge[w][j], d[j]), kxr);
         wlj = lane_next<false>(wl_edge[w][j], wrj);
-        wuj = weight(d[j], d[j + 1], k + 1 < nz ? kz : T(0));
+        wuj = weight(d[j], d[j + 1], k + 1 < nz ? hz : T(0));
       }
       T cj;
       if constexpr (XL)
