@@ -133,6 +133,24 @@ __device__ __forceinline__ double lane_value(double v, int l) {
   return join(__builtin_amdgcn_readlane(half_of(v, 0), l), __builtin_amdgcn_readlane(half_of(v, 1), l));
 }
 
+// What a workgroup decides as one, whichever of its waves sees it first:
+//  - go: whether there is work, read by one thread (another workgroup that
+//    gives up sets the done flag while this one may still be starting);
+//  - dead: the solve is given up.  It is read behind the second barrier of the
+//    sums and changes only where a barrier lies between, so every wave leaves
+//    the loop in the same iteration;
+//  - late: what a wait for the halo sets that no barrier parts from those
+//    reads (where A p is exchanged); it counts with the next sums.
+struct Fate {
+  int go, late, dead;
+};
+__device__ __forceinline__ void fate_set(const CgScalars* sc, Fate& fate) {
+  if (threadIdx.x == 0) {
+    fate.late = fate.dead = 0;
+    fate.go = !__hip_atomic_load(&sc->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && sc->bb != 0.0;
+  }
+}
+
 // A wait that other workgroups end: polls are counted, and from the 64th on
 // every 64th looks at the clock (100 MHz).
 struct Wait {
@@ -150,11 +168,13 @@ struct Wait {
 
 // The sums of all workgroups' eight values from this workgroup's per wave
 // (sh_w), in every thread: a workgroup's sums are one 128-byte line of `set`,
-// lane l holds half l % 2 of value l % 16 / 2.  True when a wait outlasted its
-// limit.  (A barrier has made sh_w visible; eight waves.)
+// lane l holds half l % 2 of value l % 16 / 2.  True when a wait, of this or
+// for the halo before it (LATE), outlasted its limit.  (A barrier has made sh_w
+// visible; eight waves.)
+template <bool LATE>
 __device__ __forceinline__ bool sums_of_all(const double (&sh_w)[8][8], double (&sh_s)[8][8],
                                             uint64_t* set, int nblk, uint32_t tag, uint64_t spin,
-                                            int* sh_dead, double (&s7)[7]) {
+                                            Fate& fate, double (&s7)[7]) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double tot = waves_sum(sh_w[lane >> 3][lane & 7]);  // value l % 8 in lane l
   if (nblk > 1) {
@@ -166,7 +186,7 @@ __device__ __forceinline__ bool sums_of_all(const double (&sh_w)[8][8], double (
     // every workgroup's sums: four lines a load, wave w the lines 4 w ..
     // of each 32, four such loads in flight
     double sum = 0.0;
-    bool late = false;
+    bool late = LATE && w == 0 && fate.late;
     for (int b = w * 4 + (lane >> 4); b < nblk; b += 128) {
       const uint64_t* const from = st + 16L * b;
       uint64_t dw[4];
@@ -189,13 +209,13 @@ __device__ __forceinline__ bool sums_of_all(const double (&sh_w)[8][8], double (
     sum = halve<32>(sum, sum);
     sum = halve<16>(sum, sum);
     if (lane < 16 && (lane & 1) == 0) sh_s[w][lane >> 1] = sum;
-    if (late) *sh_dead = 1;
+    if (late) fate.dead = 1;
     lds_barrier();
     tot = waves_sum(sh_s[lane >> 3][lane & 7]);
   }
 #pragma unroll
   for (int u = 0; u < 7; ++u) s7[u] = lane_value(tot, u);
-  return *sh_dead != 0;
+  return fate.dead != 0;
 }
 
 // what a solve leaves (one thread a workgroup)
@@ -234,8 +254,10 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
   __shared__ T dr_edge[NW][CD ? 1 : R], wl_edge[NW][CD ? 1 : R];
   __shared__ T xs[XL ? R : 1][XL ? NT : 1], cs[XL ? R : 1][XL ? NT : 1];
   __shared__ double sh_w[NW][8], sh_s[NW][8];
-  __shared__ int sh_dead;
-  if (__hip_atomic_load(&sc->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || sc->bb == 0.0) return;
+  __shared__ Fate fate;
+  fate_set(sc, fate);
+  lds_barrier();
+  if (!fate.go) return;
   const int nx = G.nx, nz = G.nz, wx = g.wx, nwz = NW / wx;
   const int W = 64 * wx, TZ = R * nwz, EW = 2 * W + 2 * TZ;  // border cells of a tile
   const int tile = xcd_block(), bx = tile % g.nbx, bz = tile / g.nbx, nblk = gridDim.x;
@@ -248,7 +270,6 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
   const T kx = K.k[0], kz = K.k[1];
   const T wx0 = CD ? v.Dc * kx : T(0), wz0 = CD ? v.Dc * kz : T(0);
   const bool in = i < nx;
-  if (t == 0) sh_dead = 0;
   for (int e = t; e < kRight + NW * R; e += NT) ring[e] = T(0);
   if (lane < (CD ? 1 : R)) dr_edge[w][lane] = wl_edge[w][lane] = T(0);
 
@@ -453,7 +474,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
     double s7[7];
     if constexpr (CD) {
       uint64_t* const st = sets + (iter & 1) * spar + (t & 15);
-      bool late = false;
+      bool late = w == 0 && fate.late;
       // the tree of k_cg_iter2 and its sum over partials: the four waves in
       // order, then workgroup b in thread b (b - 256, ...) of four waves
       double sum[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -481,15 +502,15 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
       }
       const double tot = wave_sum8(sum);
       if ((lane & 7) == 0) sh_s[w][lane >> 3] = tot;
-      if (late) sh_dead = 1;
+      if (late) fate.dead = 1;
       lds_barrier();
 #pragma unroll
       for (int u = 0; u < 7; ++u) s7[u] = ((sh_s[0][u] + sh_s[1][u]) + sh_s[2][u]) + sh_s[3][u];
     } else {
       static_assert(CD || NW == 8, "one value of one wave a lane");
-      if constexpr (!CD) sums_of_all(sh_w, sh_s, sets + (iter & 1) * spar, nblk, tag, g.spin, &sh_dead, s7);
+      if constexpr (!CD) sums_of_all<true>(sh_w, sh_s, sets + (iter & 1) * spar, nblk, tag, g.spin, fate, s7);
     }
-    if (sh_dead) {
+    if (fate.dead) {
       bad = true;
       status = kCgpAborted;
       break;
@@ -531,7 +552,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
           for (int h = 0; h < NH; ++h) ok = ok && (uint32_t)(hv[s][h] >> 32) == tag;
           if (ok) break;
           if (wt.over(g.spin)) {
-            sh_dead = 1;
+            fate.late = 1;
             break;
           }
 #pragma unroll
@@ -596,8 +617,8 @@ __global__ __launch_bounds__(512) void k_cgp3(Geo G, Stencil<3, T> K, CgSolve<T>
   __shared__ T sd[MEM ? 1 : TZ * SY * SX];
   __shared__ T zl[MEM ? NZ * NT : 1];
   __shared__ double sh_w[NW][8], sh_s[NW][8];
-  __shared__ int sh_dead;
-  if (__hip_atomic_load(&sc->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) || sc->bb == 0.0) return;
+  __shared__ Fate fate;
+  fate_set(sc, fate);
   const int nx = G.nx, ny = G.ny, nz = G.nz;
   const int tile = xcd_block(), nblk = gridDim.x;
   const int bx = tile % g.nbx, by = (tile / g.nbx) % g.nby, bz = tile / (g.nbx * g.nby);
@@ -626,12 +647,12 @@ __global__ __launch_bounds__(512) void k_cgp3(Geo G, Stencil<3, T> K, CgSolve<T>
   // would take the registers of the vectors.)
   int own = at(0, w * RY, lane), th = t, plane = nx * ny, kb = k0;
   auto off = [](int k, int y, int x) { return (k * SY + y) * SX + x; };
-  if (t == 0) sh_dead = 0;
   for (int e = t; e < TZ * SY * SX; e += NT) {
     sp[e] = T(0);
     if constexpr (!MEM) sd[e] = T(0);
   }
   __syncthreads();
+  if (!fate.go) return;
 
   // ---- halo cells of this thread: [0, NZ) below and above its columns, then
   // of the y sides, then of the x sides
@@ -989,7 +1010,7 @@ __global__ __launch_bounds__(512) void k_cgp3(Geo G, Stencil<3, T> K, CgSolve<T>
     if ((lane & 7) == 0) sh_w[w][lane >> 3] = ws;
     lds_barrier();
     double s7[7];
-    const bool late = sums_of_all(sh_w, sh_s, sets + (iter & 1) * spar, nblk, tag, g.spin, &sh_dead, s7);
+    const bool late = sums_of_all<HQ>(sh_w, sh_s, sets + (iter & 1) * spar, nblk, tag, g.spin, fate, s7);
     if (late) {
       bad = true;
       status = kCgpAborted;
@@ -1109,7 +1130,7 @@ __global__ __launch_bounds__(512) void k_cgp3(Geo G, Stencil<3, T> K, CgSolve<T>
           for (int u = 0; u < NH; ++u) ok = ok && (uint32_t)(hw[u] >> 32) == tag;
           if (ok) break;
           if (wt.over(g.spin)) {
-            sh_dead = 1;
+            (HQ ? fate.late : fate.dead) = 1;
             break;
           }
 #pragma unroll

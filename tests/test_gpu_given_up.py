@@ -1,0 +1,39 @@
+"""One-launch solves that are given up (a workgroup's wait outlasts the limit,
+here 0: at its first poll): the call is done again with one launch an
+iteration, which the launch counts show, and its result is the solve's."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import cfg_mesh, gea_mod, pair  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def context(oracle_lib, gea_mod, dims, solver, **par):  # noqa: F811
+    nx, ny, nz = dims
+    name = "bubble3d_256x256x128" if ny else "bubble2d_64x32"
+    cfg = cfg_mesh(name, nx, nz, ny or None, **par)
+    print(f"[given up] {dims} {solver}", flush=True)
+    return (*pair(oracle_lib, gea_mod, cfg, solver=solver), cfg)
+
+
+# every form of the exchange: A p in 2D and 3D, the direction in 3D, vectors on
+# the chip and in memory; many workgroups of which some end well
+@pytest.mark.parametrize("dims,solver", [((300, 0, 70), "pcg64"), ((1000, 0, 700), "pcg64"), ((700, 0, 450), "mixed"),
+                                         ((90, 60, 40), "pcg64"), ((128, 128, 100), "pcg64"),
+                                         ((150, 90, 61), "mixed"), ((250, 110, 250), "mixed")])
+def test_a_given_up_solve_is_done_again(oracle_lib, gea_mod, dims, solver):  # noqa: F811
+    tol = 1e-11 if solver == "pcg64" else 1e-9
+    O, s, S, cfg = context(oracle_lib, gea_mod, dims, solver, tol=tol, max_iter=100000)
+    assert S.L.gea_set_wait_limit(S.ctx, 0) == 0
+    S.kernel_timing(True)
+    x = s.pp.copy()
+    st = S.pressure_solve(x)
+    launches = S.kernel_times()[1][0 if solver == "pcg64" else 2]
+    S.kernel_timing(False)
+    c, D, b = S.get_fields(gea_mod.FIELD_C | gea_mod.FIELD_D | gea_mod.FIELD_B)
+    S.close()
+    assert st.status == 0 and st.iters > 0
+    assert launches > st.iters  # (one an iteration, and the given-up solve)
+    # (the recursive residual of the FP64 form is within a tenth of 1e-11 of the true one)
+    assert np.linalg.norm(b - O.apply_A(c, D, x)) <= (1.1 if solver == "pcg64" else 1.001) * tol * np.linalg.norm(b)
