@@ -580,12 +580,21 @@ void hold_card(gea_ctx* x, const CgpPlan& p) {
 }
 
 // A one-launch solve gave up waiting: from here on this context takes the
-// iteration kernels, and the call is done again with them.
+// iteration kernels, and the call is done again with them.  The words it left
+// carry tags that the next launch would use (a launch that gives up does not
+// move the last tag on): they are cleared.  A deferred solve enqueued behind it
+// may have run on them; every deferred solve of the step is looked at before any
+// is acted on, so nothing of that step counts.
 struct CgpAborted {};
 void check_cgp(gea_ctx* x, const CgScalars& hs) {
   if (hs.status != kCgpAborted) return;
   x->plan_e = x->plan64 = x->plan32 = CgpPlan{};
+  HIPCHK(hipMemsetAsync(x->cgx, 0, sizeof(uint64_t) * (size_t)cgp_words(x->G), x->stream));
   throw CgpAborted{};
+}
+// the same for all solves of a step whose scalars have been read
+void check_deferred(gea_ctx* x) {
+  for (int k = 0; k < x->ndeferred; ++k) check_cgp(x, x->deferred[k].hs);
 }
 
 // Host loop of one CG solve: enqueue batches of iterations, read the device
@@ -709,6 +718,16 @@ void cast_system(gea_ctx* x) {
     launch_cast_coeffs(x->stream, x->G, x->c, x->D, x->dinv, x->c32, x->D32, x->dinv32);
   });
   x->sys32 = true;
+}
+
+// The scalars of deferred solves that no read has delivered, behind a wait for
+// the stream; other snapshots are dropped (whoever took them may be gone).
+void take_deferred(gea_ctx* x) {
+  for (int k = 0; k < x->nsnap; ++k)
+    for (gea_ctx::Deferred& d : x->deferred)
+      if (x->snaps[k].host == &d.hs)
+        std::memcpy(&d.hs, x->pin + gea_ctx::kSnapBase + gea_ctx::kSnapSlot * k, sizeof d.hs);
+  x->nsnap = 0;
 }
 
 // A one-launch solve just enqueued: its scalars wait for a later read.
@@ -1461,9 +1480,9 @@ gea_status step_once(gea_ctx* x, gea_step_stats* stats, bool* redo) {
     hs = x->last_h64;
   else
     read_scalars(x, x->sc, &hs);
+  check_deferred(x);  // (all of them before any is acted on)
   for (int k = 0; k < x->ndeferred; ++k) {
     const gea_ctx::Deferred& d = x->deferred[k];
-    check_cgp(x, d.hs);
     if (!d.hs.done || d.hs.status != 0 || d.hs.bb == 0.0) {
       *redo = true;
       return GEA_OK;
@@ -1514,7 +1533,8 @@ gea_status step_deferred(gea_ctx* x, gea_step_stats* stats) {
   x->defer = false;
   HIPCHK(hipStreamSynchronize(x->stream));
   if (x->big.owns_lock()) x->big.unlock();
-  x->nsnap = 0;
+  take_deferred(x);
+  check_deferred(x);  // (one may have been given up beside what ended the step)
   x->ndeferred = 0;
   x->tail = nullptr;
   x->res_parts = 0;

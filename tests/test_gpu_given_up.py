@@ -37,3 +37,28 @@ def test_a_given_up_solve_is_done_again(oracle_lib, gea_mod, dims, solver):  # n
     assert launches > st.iters  # (one an iteration, and the given-up solve)
     # (the recursive residual of the FP64 form is within a tenth of 1e-11 of the true one)
     assert np.linalg.norm(b - O.apply_A(c, D, x)) <= (1.1 if solver == "pcg64" else 1.001) * tol * np.linalg.norm(b)
+
+
+# A solve given up in a step that ends with another solve's error: behind it (a
+# single workgroup's refined pressure solve behind a given-up energy sweep), or
+# before it (an energy sweep short of iterations before a given-up pressure
+# solve).  The step is rolled back, and what the given-up launch left in the
+# exchange area is not taken for a later solve's.
+@pytest.mark.parametrize("dims,solver,max_iter", [((64, 0, 32), "mixed", 3), ((200, 0, 16), "pcg64", 1)])
+def test_given_up_beside_another_error(oracle_lib, gea_mod, dims, solver, max_iter):  # noqa: F811
+    tol = 1e-11 if solver == "pcg64" else 1e-9
+    O, s, S, cfg = context(oracle_lib, gea_mod, dims, solver, tol=tol, max_iter=max_iter)
+    before = S.state()
+    assert S.L.gea_set_wait_limit(S.ctx, 0) == 0
+    for _ in range(2):
+        assert S.step_status(1)[0] == gea_mod.ERR_NOCONV
+        for f, v in S.state().items():
+            assert np.array_equal(before[f], v), f
+    assert S.L.gea_set_wait_limit(S.ctx, 25000000) == 0
+    S.set_solver(solver, tol, max_iter=100000)
+    assert S.step(3).steps_done == 3
+    x = np.ascontiguousarray(S.state()["pp"])
+    assert S.pressure_solve(x).status == 0
+    c, D, b = S.get_fields(gea_mod.FIELD_C | gea_mod.FIELD_D | gea_mod.FIELD_B)
+    S.close()
+    assert np.linalg.norm(b - O.apply_A(c, D, x)) <= (1.1 if solver == "pcg64" else 1.001) * tol * np.linalg.norm(b)
