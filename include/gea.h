@@ -37,6 +37,12 @@
  *    gea_init_mesh.  gea_step, gea_pressure_solve and gea_init_bubble return
  *    after the work completed (convergence is decided from device values);
  *    device-to-device copies are ordered on the stream.
+ *  - Contexts on one GPU may run from several threads, each on its own
+ *    stream.  Where a mesh's whole solve is one launch, its workgroups wait
+ *    for each other, so such solves share the card out: one is enqueued when
+ *    its share is free, and holds it until the host has read its end, behind
+ *    whatever its stream held before.  Another context's solve that needs
+ *    that share waits meanwhile, on the host.
  *  - Errors: every call returns a gea_status; no C++ exception crosses the
  *    ABI; gea_last_error gives a message.  A step that fails (no
  *    convergence within max_iter, a non-finite value) leaves the state as it

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
 #include <functional>
@@ -292,7 +293,11 @@ struct gea_ctx {
   bool defer = false;
   uint64_t spin = kCgpSpin;  // how long a workgroup of theirs waits (gea_set_wait_limit)
   int dev = 0;
-  std::unique_lock<std::mutex> big;  // see hold_card
+  int held = 0;  // share of the card that a solve on the stream has (see hold_card)
+  void give_card() {
+    card_give(dev, held);
+    held = 0;
+  }
   // pinned host buffer the solver scalars are read through (device-to-host
   // copies into it are asynchronous, so several go out with one wait)
   char* pin = nullptr;
@@ -345,9 +350,37 @@ Geo make_geo(const gea_mesh& m) {
 namespace gea {
 Geo mesh_geo(const gea_mesh& m) { return make_geo(m); }
 void set_call_error(const std::string& msg) { g_init_error = msg; }
-std::mutex& card_mutex(int dev) {
-  static std::mutex m[64];
-  return m[dev & 63];
+
+namespace {
+struct Card {
+  std::mutex mu;
+  std::condition_variable cv;
+  uint64_t next = 0, serving = 0;
+  int used = 0;
+};
+Card& card_of(int dev) {
+  static Card c[64];
+  return c[dev & 63];
+}
+}  // namespace
+void card_take(int dev, int share) {
+  if (share == 0) return;
+  Card& c = card_of(dev);
+  std::unique_lock<std::mutex> lock(c.mu);
+  const uint64_t mine = c.next++;
+  c.cv.wait(lock, [&] { return c.serving == mine && c.used + share <= kCardShares; });
+  c.used += share;
+  ++c.serving;
+  c.cv.notify_all();
+}
+void card_give(int dev, int share) {
+  if (share == 0) return;
+  Card& c = card_of(dev);
+  {
+    std::lock_guard<std::mutex> lock(c.mu);
+    c.used -= share;
+  }
+  c.cv.notify_all();
 }
 }  // namespace gea
 
@@ -554,7 +587,7 @@ void read_structs(gea_ctx* x, const Extra* parts, int n) {
     }
   }
   wait_stream(x);
-  if (x->big.owns_lock()) x->big.unlock();  // (no one-launch solve is left on the stream)
+  x->give_card();  // (no one-launch solve is left on the stream)
   off = 0;
   for (int k = 0; k < n; ++k) {
     std::memcpy(parts[k].host, x->pin + off, parts[k].bytes);
@@ -573,10 +606,15 @@ void read_scalars(gea_ctx* x, CgScalars* dev, CgScalars* host, const Extra& extr
   read_structs(x, parts, extra.bytes ? 2 : 1);
 }
 
-// (see kSharedBlocks) held from here to this context's next read
-void hold_card(gea_ctx* x, const CgpPlan& p) {
-  if (p.blocks > kSharedBlocks && !x->big.owns_lock())
-    x->big = std::unique_lock<std::mutex>(card_mutex(x->dev));
+// The card's share for a one-launch solve (see kCardShares), held from here to
+// this context's next read.  Several solves may go out before that, one after
+// the other on the stream: the share is that of the largest of the context's
+// plans, as one that had to be added to would wait for itself.
+void hold_card(gea_ctx* x) {
+  if (x->held) return;
+  const int share = std::max({x->plan_e.share, x->plan64.share, x->plan32.share});
+  card_take(x->dev, share);
+  x->held = share;
 }
 
 // A one-launch solve gave up waiting: from here on this context takes the
@@ -755,7 +793,7 @@ gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
   CgVectors<double> v{xv, x->r, x->r1, x->p0, x->p1, x->q, x->q1, x->c, x->D, x->dinv, x->b};
   x->timer.run(4, x->stream, [&] { cg_init<double>(x->stream, G, v, w, x->prm.tol, x->prm.max_iter); });
   if (x->plan64.variant) {
-    hold_card(x, x->plan64);
+    hold_card(x);
     x->timer.run(0, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan64, x->cgx, x->spin, x->sc); });
     if (deferred(x, x->corr, 0)) {
       HIPCHK(hipGetLastError());
@@ -818,7 +856,7 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
   bool timed = false;
   auto whole = [&] {
     timed = x->prm.solver == GEA_LEARNED_MIXED && x->t_iter_ms < 0;
-    hold_card(x, x->plan32);
+    hold_card(x);
     if (timed) HIPCHK(hipEventRecord(x->ev_it[0], x->stream));
     x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32); });
     if (timed) HIPCHK(hipEventRecord(x->ev_it[1], x->stream));
@@ -1041,7 +1079,7 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
   };
   const bool one = x->plan32.variant != 0;
   auto whole = [&] {
-    hold_card(x, x->plan32);
+    hold_card(x);
     x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32); });
   };
   // network step(s), then Jacobi-PCG resumed from their iterate and residual
@@ -1229,7 +1267,7 @@ gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters
   });
   CgScalars hs{};  // rr = 0: the first read supplies the starting residual
   if (x->plan_e.variant) {
-    hold_card(x, x->plan_e);
+    hold_card(x);
     x->timer.run(7, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan_e, x->cgx, x->spin, w.sc); });
     if (deferred(x, -1, sweep)) {
       HIPCHK(hipGetLastError());
@@ -1532,7 +1570,7 @@ gea_status step_deferred(gea_ctx* x, gea_step_stats* stats) {
   if (!redo && (rc == GEA_OK || x->ndeferred == 0)) return rc;
   x->defer = false;
   HIPCHK(hipStreamSynchronize(x->stream));
-  if (x->big.owns_lock()) x->big.unlock();
+  x->give_card();
   take_deferred(x);
   check_deferred(x);  // (one may have been given up beside what ended the step)
   x->ndeferred = 0;
@@ -1569,9 +1607,7 @@ template <typename F>
 gea_status guarded(gea_ctx* x, F&& f) {
   struct Release {  // (an error may leave with the card held)
     gea_ctx* x;
-    ~Release() {
-      if (x->big.owns_lock()) x->big.unlock();
-    }
+    ~Release() { x->give_card(); }
   } release{x};
   try {
     try {

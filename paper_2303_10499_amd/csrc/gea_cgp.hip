@@ -1325,6 +1325,8 @@ CgpPlan cgp_plan(const Geo& G, bool cd) {
     // (a single workgroup exchanges nothing: worth twice the rows, not more)
     if (!cd && G.ndim == 2 && p.blocks > 1 && k + 1 < n && V[k + 1].rows <= 4 && tiles(G, V[k + 1]).blocks == 1) continue;
     p.variant = k + 1;
+    const int die = cus / 8 > 0 ? cus / 8 : 1, n8 = (p.blocks + 7) / 8;  // a die's compute units, what the launch takes of them
+    p.share = p.blocks == 1 ? 0 : (n8 >= die ? kCardShares : (kCardShares * n8 + die - 1) / die);
     return p;
   }
   return CgpPlan{};

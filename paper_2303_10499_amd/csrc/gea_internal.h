@@ -253,14 +253,21 @@ bool cg_folds(const CgWork& w);
 constexpr int kCgpAborted = -100;           // status: a wait for another workgroup outlasted kCgpSpin
 constexpr uint64_t kCgpSpin = 25000000ull;  // 0.25 s of the 100 MHz clock
 // Two one-launch solves of two streams that each hold part of the card and
-// wait for the rest of their workgroups would both run into that limit: a
-// launch of more workgroups than this holds the card's mutex from its
-// enqueueing to the host's read of its end.  (Smaller ones fit beside each
-// other: a process has four hardware queues.)
-constexpr int kSharedBlocks = 48;
+// wait for the rest of their workgroups would both run into that limit,
+// whatever their sizes.  So each takes its share of the card before it is
+// enqueued and gives it back when the host has read its end, and the shares
+// out at a time never pass the card: a compute unit for every workgroup.  The
+// workgroups of a launch go to the 8 dies in turn, so a launch of n takes
+// ceil(n / 8) of each die's compute units (32 on this card), one that fills
+// them all, and a single workgroup, which waits for no other, none.  Shares are
+// given in the order they were asked for.
+constexpr int kCardShares = 32;
+void card_take(int dev, int share);
+void card_give(int dev, int share);
 struct CgpPlan {
   int variant;  // 1 + index of the kernel, 0: none
   int wx, nbx, nby, blocks;
+  int share;    // of the card, in kCardShares
   long words;   // 64-bit words of the exchange area, zero before its first launch
 };
 template <typename T>

@@ -19,7 +19,6 @@ namespace gea {
 // defined in gea_api.hip
 Geo mesh_geo(const gea_mesh& m);
 void set_call_error(const std::string& msg);
-std::mutex& card_mutex(int dev);
 
 namespace {
 
@@ -174,9 +173,17 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
   const bool one = plan.variant && plan.words <= kStaticExchange;
   int dev = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e, "hipGetDevice");
-  std::unique_lock<std::mutex> alone(card_mutex(dev), std::defer_lock);
+  struct Share {
+    int dev, n;
+    void give() {
+      card_give(dev, n);
+      n = 0;
+    }
+    ~Share() { give(); }
+  } share{dev, 0};
   if (one) {
-    if (plan.blocks > kSharedBlocks) alone.lock();
+    card_take(dev, plan.share);
+    share.n = plan.share;
     cgp_solve<double>(s, G, v, plan, ex, kCgpSpin, sc);
   }
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve set-up");
@@ -195,7 +202,7 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve set-up");
     if ((e = read()) != hipSuccess) return hip_fail(e, "reading the solver scalars");
   }
-  if (alone.owns_lock()) alone.unlock();
+  share.give();
   stats->rel_res0 = hs.bb > 0 ? std::sqrt(hs.rr0 / hs.bb) : 0.0;
   if (hs.bb == 0.0) {  // b = 0: x = 0
     hipLaunchKernelGGL(k_static_fill, dim3(grid_for(G.nc)), dim3(kBlock), 0, s, (long)G.nc, x, 0.0);

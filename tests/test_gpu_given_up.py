@@ -62,3 +62,43 @@ def test_given_up_beside_another_error(oracle_lib, gea_mod, dims, solver, max_it
     c, D, b = S.get_fields(gea_mod.FIELD_C | gea_mod.FIELD_D | gea_mod.FIELD_B)
     S.close()
     assert np.linalg.norm(b - O.apply_A(c, D, x)) <= (1.1 if solver == "pcg64" else 1.001) * tol * np.linalg.norm(b)
+
+
+# A launch that needs most of the card beside small ones on other streams, each
+# partly placed, would wait for each other: their shares keep them apart (no
+# solve takes one launch an iteration), and nothing else changes.
+def test_large_and_small_solves_at_once(gea_mod):  # noqa: F811
+    import threading
+
+    import torch
+    jobs = [((600, 400), 12), ((300, 70), 40), ((200, 120), 40)]  # about 250, 25 and 32 workgroups
+    cfgs = [cfg_mesh("paper_smooth_5m", nx, nz, tol=1e-10) for (nx, nz), _ in jobs]
+
+    def run(k):
+        S = gea_mod.Solver(cfgs[k]["mesh"], cfgs[k]["params"], solver="pcg64")
+        S.init_bubble(**cfgs[k]["bubble"])
+        S.kernel_timing(True)
+        st = S.step(jobs[k][1])
+        launches = S.kernel_times()[1]
+        S.kernel_timing(False)
+        out = S.state()
+        S.close()
+        return st, launches, out
+
+    alone = [run(k) for k in range(3)]
+    got = [None] * 3
+
+    def work(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got[k] = run(k)
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for (st, launches, out), (_, _, want) in zip(got, alone):
+        assert launches[0] == st.total_solves  # (pressure solves; class 7: a set-up and a solve a sweep)
+        assert launches[7] == 4 * st.steps_done
+        for f, v in want.items():
+            assert np.array_equal(out[f], v), f
