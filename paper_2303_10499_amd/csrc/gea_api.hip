@@ -851,14 +851,16 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     x->timer.run(2, x->stream, [&] { cg_iter_kernel<float>(x->stream, G, v, j, w, fold); });
     if (last || !cg_folds(w)) x->timer.run(3, x->stream, [&] { cg_scalars(x->stream, G, j, w); });
   };
-  // the whole inner solve in one launch, where the mesh has a plan for it
+  // The whole inner solve in one launch, where the mesh has a plan for it.
+  // (The check before it may have been enqueued behind an inner solve that was
+  // read since: the cap on the sum of the iterations is this launch's then.)
   const bool one = x->plan32.variant != 0;
   bool timed = false;
   auto whole = [&] {
     timed = x->prm.solver == GEA_LEARNED_MIXED && x->t_iter_ms < 0;
     hold_card(x);
     if (timed) HIPCHK(hipEventRecord(x->ev_it[0], x->stream));
-    x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32); });
+    x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32, x->prm.max_iter - total); });
     if (timed) HIPCHK(hipEventRecord(x->ev_it[1], x->stream));
   };
   auto time_whole = [&](int iters) {  // (after the read that covers it)
@@ -881,7 +883,8 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     // behind an unread inner solve the check acts only if that solve is done
     residual_check(x, xv, v, budget, true, unread ? x->sc32 : nullptr);
     HIPCHK(hipGetLastError());
-    if (!unread && (one ? !x->predict_conv(outer) : last32_of(outer) > 0 && x->predict_unconv(outer))) {
+    if (!unread && total < x->prm.max_iter &&
+        (one ? !x->predict_conv(outer) : last32_of(outer) > 0 && x->predict_unconv(outer))) {
       // (were this check converged after all, the inner system starts done,
       // its iterate zero, and the correction adds zero)
       snapshot(x, x->sc, &s_res, sizeof s_res);
@@ -1078,9 +1081,9 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
     if (last || !cg_folds(w)) x->timer.run(3, x->stream, [&] { cg_scalars(x->stream, G, j, w); });
   };
   const bool one = x->plan32.variant != 0;
-  auto whole = [&] {
+  auto whole = [&] {  // (its cap: as in solve_mixed)
     hold_card(x);
-    x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32); });
+    x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32, x->prm.max_iter - total); });
   };
   // network step(s), then Jacobi-PCG resumed from their iterate and residual
   // (when the flexible CG has converged the resumed solve starts done and its

@@ -370,7 +370,7 @@ __global__ __launch_bounds__(64 * NW) void k_cgp2(Geo G, Stencil<2, T> K, CgSolv
   const long epar = (long)nblk * EW * NH, spar = 16L * nblk;  // words of one parity
   uint64_t* const my_edge = edges + (long)tile * EW * NH;
   const double tolbb = sc->tol2 * sc->bb;
-  const int max_iter = sc->max_iter;
+  const int max_iter = min(sc->max_iter, g.cap);
 
 #pragma unroll
   for (int j = 0; j < R; ++j) p[j] = r[j] * m[j];
@@ -842,7 +842,7 @@ __global__ __launch_bounds__(512) void k_cgp3(Geo G, Stencil<3, T> K, CgSolve<T>
   // (uniform) neighbours in z
   const bool zl_nb = bz > 0, zh_nb = k0 + TZ < nz;
   const double tolbb = sc->tol2 * sc->bb;
-  const int max_iter = sc->max_iter;
+  const int max_iter = min(sc->max_iter, g.cap);
   constexpr int GX = R < 8 ? R : 8;  // x of these cells in flight (MEM)
   // (MEM) one load of a wave that names 64 of the 128-byte lines it reads later:
   // it brings them into the L2 in the meantime, for one register.  D and c of
@@ -1354,14 +1354,14 @@ template CgpPlan cgp_plan<float>(const Geo&, bool);
 
 template <typename T>
 void cgp_solve(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgpPlan& p, uint64_t* ex,
-               uint64_t spin, CgScalars* sc) {
+               uint64_t spin, CgScalars* sc, int cap) {
   int n = 0;
   const Variant<T>& V = variants<T>(&n)[p.variant - 1];
   const CgSolve<T> a{v.x, v.r, v.c, v.D, v.dinv, v.Dc, v.xo};
-  const CgpGrid g{ex, spin, p.wx, p.nbx, p.nby};
+  const CgpGrid g{ex, spin, cap, p.wx, p.nbx, p.nby};
   V.run(s, G, a, p, g, sc);
 }
-template void cgp_solve<double>(hipStream_t, const Geo&, const CgVectors<double>&, const CgpPlan&, uint64_t*, uint64_t, CgScalars*);
-template void cgp_solve<float>(hipStream_t, const Geo&, const CgVectors<float>&, const CgpPlan&, uint64_t*, uint64_t, CgScalars*);
+template void cgp_solve<double>(hipStream_t, const Geo&, const CgVectors<double>&, const CgpPlan&, uint64_t*, uint64_t, CgScalars*, int);
+template void cgp_solve<float>(hipStream_t, const Geo&, const CgVectors<float>&, const CgpPlan&, uint64_t*, uint64_t, CgScalars*, int);
 
 }  // namespace gea

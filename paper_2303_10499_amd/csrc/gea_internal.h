@@ -283,14 +283,18 @@ struct CgSolve {
 struct CgpGrid {
   uint64_t* ex;   // the exchange area; word 0: the last tag used
   uint64_t spin;
+  int cap;        // iterations, beside the scalars' max_iter
   int wx, nbx, nby;
 };
 template <typename T>
 CgpPlan cgp_plan(const Geo& G, bool cd);
 long cgp_words(const Geo& G);  // the most that a plan on the mesh needs, on any device
+// spin: limit of a wait (0: none is waited).  cap: the iterations left, where
+// the scalars' max_iter was set before the host knew them (a refined solve's
+// check behind an inner solve that it has not read)
 template <typename T>
 void cgp_solve(hipStream_t s, const Geo& G, const CgVectors<T>& v, const CgpPlan& p, uint64_t* ex,
-               uint64_t spin, CgScalars* sc);  // spin: limit of a wait (0: none is waited)
+               uint64_t spin, CgScalars* sc, int cap = 0x7fffffff);
 
 // Jacobi-PCG resumed on the FP32 inner system from its current iterate and
 // residual, keeping the set-up's ||b||^2 and tolerance: its scalars from
