@@ -299,11 +299,16 @@ gea_status gea_time_solver_kernels(gea_ctx* ctx, int32_t reps, double* ms);
 gea_status gea_time_network(gea_ctx* ctx, int32_t reps, double* ms, double* gflop);
 
 /* Test support: how long (in 10 ns) a workgroup of a one-launch pressure or
- * energy solve waits for another one before the solve is given up and the
- * call done again with one launch an iteration; 0: not at all.  (By default
- * 0.25 s: its workgroups need to be on the card at the same time, which
- * another program's kernels can prevent.) */
+ * energy solve waits for another one before the solve is given up; 0: not at
+ * all.  (By default 0.25 s: its workgroups need to be on the card at the same
+ * time, which another program's kernels can prevent.)  The step, or the call,
+ * is then done again with one launch an iteration, and the context's next
+ * steps or solves are done so too, 64 with that one: twice as many each further
+ * time, up to 65536, half as many again after as many without one. */
 gea_status gea_set_wait_limit(gea_ctx* ctx, uint64_t ticks);
+
+/* How often this context has given one-launch solves up so far. */
+gea_status gea_given_up(gea_ctx* ctx, int64_t* count);
 
 /* For callers that cannot allocate device memory (work under HIP graph
  * capture, serving loops, harnesses that forbid hipMalloc): the FP64

@@ -280,6 +280,24 @@ struct gea_ctx {
   // (variant 0 where the mesh takes the iteration kernels) and their exchange area
   CgpPlan plan_e{}, plan64{}, plan32{};
   uint64_t* cgx = nullptr;
+  // Once one of them is given up (its workgroups were not on the card together
+  // for 0.25 s, see kCgpSpin), the next `pause` steps or solves take the
+  // iteration kernels; the pause doubles with each time and halves after as many
+  // steps without one.  (64 steps of one launch an iteration lose some 10 to 100
+  // ms, less than a give-up costs; 2^16 bound what a card that is always shared
+  // loses to trying again.)
+  static constexpr int kPauseFirst = 64, kPauseMost = 1 << 16;
+  int pause = kPauseFirst, paused = 0, unbroken = 0;
+  int64_t given_up = 0;
+  void begin_solves() {  // a step's, or those of a call of its own
+    if (paused > 0) {
+      --paused;
+    } else if (++unbroken >= pause) {
+      unbroken = 0;
+      pause = std::max(pause / 2, kPauseFirst);
+    }
+  }
+  bool one_launch(const CgpPlan& p) const { return p.variant && paused == 0; }
   // One-launch solves of a step whose scalars are read with the step's last
   // read (see step_deferred): on while `defer`, off for `eager_steps` more steps
   // once one of them did not end well
@@ -617,8 +635,8 @@ void hold_card(gea_ctx* x) {
   x->held = share;
 }
 
-// A one-launch solve gave up waiting: from here on this context takes the
-// iteration kernels, and the call is done again with them.  The words it left
+// A one-launch solve gave up waiting: the step, or the call, is done again with
+// the iteration kernels, and so are the next ones for a while.  The words it left
 // carry tags that the next launch would use (a launch that gives up does not
 // move the last tag on): they are cleared.  A deferred solve enqueued behind it
 // may have run on them; every deferred solve of the step is looked at before any
@@ -626,7 +644,10 @@ void hold_card(gea_ctx* x) {
 struct CgpAborted {};
 void check_cgp(gea_ctx* x, const CgScalars& hs) {
   if (hs.status != kCgpAborted) return;
-  x->plan_e = x->plan64 = x->plan32 = CgpPlan{};
+  ++x->given_up;
+  x->paused = x->pause;
+  x->pause = std::min(2 * x->pause, gea_ctx::kPauseMost);
+  x->unbroken = 0;
   HIPCHK(hipMemsetAsync(x->cgx, 0, sizeof(uint64_t) * (size_t)cgp_words(x->G), x->stream));
   throw CgpAborted{};
 }
@@ -792,7 +813,7 @@ gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
   const CgWork& w = x->w64;
   CgVectors<double> v{xv, x->r, x->r1, x->p0, x->p1, x->q, x->q1, x->c, x->D, x->dinv, x->b};
   x->timer.run(4, x->stream, [&] { cg_init<double>(x->stream, G, v, w, x->prm.tol, x->prm.max_iter); });
-  if (x->plan64.variant) {
+  if (x->one_launch(x->plan64)) {
     hold_card(x);
     x->timer.run(0, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan64, x->cgx, x->spin, x->sc); });
     if (deferred(x, x->corr, 0)) {
@@ -854,7 +875,7 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
   // The whole inner solve in one launch, where the mesh has a plan for it.
   // (The check before it may have been enqueued behind an inner solve that was
   // read since: the cap on the sum of the iterations is this launch's then.)
-  const bool one = x->plan32.variant != 0;
+  const bool one = x->one_launch(x->plan32);
   bool timed = false;
   auto whole = [&] {
     timed = x->prm.solver == GEA_LEARNED_MIXED && x->t_iter_ms < 0;
@@ -1080,7 +1101,7 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
     x->timer.run(2, x->stream, [&] { cg_iter_kernel<float>(x->stream, G, v, j, w, fold); });
     if (last || !cg_folds(w)) x->timer.run(3, x->stream, [&] { cg_scalars(x->stream, G, j, w); });
   };
-  const bool one = x->plan32.variant != 0;
+  const bool one = x->one_launch(x->plan32);
   auto whole = [&] {  // (its cap: as in solve_mixed)
     hold_card(x);
     x->timer.run(2, x->stream, [&] { cgp_solve<float>(x->stream, G, v, x->plan32, x->cgx, x->spin, x->sc32, x->prm.max_iter - total); });
@@ -1269,7 +1290,7 @@ gea_status solve_energy(gea_ctx* x, double* T, int nparts, int sweep, int* iters
     cg_start_from(x->stream, w.u[1], nparts, w.b, kEnergyTol, x->prm.max_iter, w.sc);
   });
   CgScalars hs{};  // rr = 0: the first read supplies the starting residual
-  if (x->plan_e.variant) {
+  if (x->one_launch(x->plan_e)) {
     hold_card(x);
     x->timer.run(7, x->stream, [&] { cgp_solve<double>(x->stream, G, v, x->plan_e, x->cgx, x->spin, w.sc); });
     if (deferred(x, -1, sweep)) {
@@ -1586,6 +1607,7 @@ gea_status step_deferred(gea_ctx* x, gea_step_stats* stats) {
 
 gea_status one_step(gea_ctx* x, gea_step_stats* stats) {
   const gea_step_stats before = *stats;
+  x->begin_solves();
   try {
     return step_deferred(x, stats);
   } catch (const CgpAborted&) {  // (the step is done again: counted once)
@@ -1836,6 +1858,7 @@ gea_status gea_pressure_solve(gea_ctx* x, const double* b, double* xv, gea_ptr_k
   gea_solve_stats local{};
   gea_solve_stats* st = stats ? stats : &local;
   return guarded(x, [&]() {
+    x->begin_solves();
     const Geo& G = x->G;
     hipStream_t s = x->stream;
     const State& S = x->st[x->cur];
@@ -2035,6 +2058,12 @@ gea_status gea_set_wait_limit(gea_ctx* x, uint64_t ticks) {
   return GEA_OK;
 }
 
+gea_status gea_given_up(gea_ctx* x, int64_t* count) {
+  if (!x || !count) return GEA_ERR_ARG;
+  *count = x->given_up;
+  return GEA_OK;
+}
+
 gea_status gea_load_weights(gea_ctx* x, const float* params, gea_ptr_kind kind) {
   if (!x) return GEA_ERR_ARG;
   if (!params) return fail(x, GEA_ERR_ARG, "null params");
@@ -2060,6 +2089,7 @@ gea_status gea_make_pair(gea_ctx* x, double rel_tol, float* in_r, float* in_a, f
   if (!in_r || !in_a || !out_d || !(rel_tol > 0)) return fail(x, GEA_ERR_ARG, "bad pair arguments");
   if (!x->has_state) return fail(x, GEA_ERR_STATE, "no state");
   return guarded(x, [&]() {
+    x->begin_solves();
     const Geo& G = x->G;
     hipStream_t s = x->stream;
     const State& S = x->st[x->cur];

@@ -101,6 +101,7 @@ def lib():
         L.gea_time_solver_kernels.argtypes = [vp, C.c_int32, P(C.c_double)]
         L.gea_time_network.argtypes = [vp, C.c_int32, P(C.c_double), P(C.c_double)]
         L.gea_set_wait_limit.argtypes = [vp, C.c_uint64]
+        L.gea_given_up.argtypes = [vp, P(C.c_int64)]
         L.gea_state_extrema.argtypes = [vp, P(Extrema)]
         L.gea_pressure_solve_static.argtypes = [P(Mesh), dp, dp, dp, dp, C.c_double, C.c_int32,
                                                 vp, P(SolveStats)]
@@ -113,7 +114,7 @@ def lib():
                      "gea_apply_pressure_operator", "gea_get_fields", "gea_kernel_timing",
                      "gea_kernel_times", "gea_time_solver_kernels", "gea_time_network",
                      "gea_pressure_solve_static", "gea_state_extrema", "gea_set_face_flux",
-                     "gea_set_history", "gea_set_wait_limit"):
+                     "gea_set_history", "gea_set_wait_limit", "gea_given_up"):
             getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
@@ -284,6 +285,12 @@ class Solver:
         n = (C.c_int64 * 8)()
         self._check(self.L.gea_kernel_times(self.ctx, ms, n), self.ctx)
         return list(ms), list(n)
+
+    def given_up(self):
+        """how often one-launch solves were given up (see gea_set_wait_limit)"""
+        n = C.c_int64()
+        self._check(self.L.gea_given_up(self.ctx, C.byref(n)), self.ctx)
+        return n.value
 
     def time_solver_kernels(self, reps=50):
         """average ms per launch: FP64 spmv, FP64 update, FP32 spmv, FP32 update"""

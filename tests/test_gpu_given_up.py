@@ -102,3 +102,31 @@ def test_large_and_small_solves_at_once(gea_mod):  # noqa: F811
         assert launches[7] == 4 * st.steps_done
         for f, v in want.items():
             assert np.array_equal(out[f], v), f
+
+
+# One give-up is not for good: the steps after it pause, twice as long after the
+# next, and then take one launch a solve again; the count tells.
+@pytest.mark.parametrize("dims", [(64, 0, 32), (300, 0, 70), (40, 24, 20)])
+def test_one_launch_solves_come_back(oracle_lib, gea_mod, dims):  # noqa: F811
+    S = context(oracle_lib, gea_mod, dims, "pcg64", tol=1e-11)[2]
+
+    def one_launch_a_solve(steps):  # (a step of two pressure solves takes more than two iterations)
+        S.kernel_timing(True)
+        st = S.step(steps)
+        n = S.kernel_times()[1][0]
+        S.kernel_timing(False)
+        assert n == st.total_solves or n >= st.total_iters > st.total_solves
+        return n == st.total_solves
+
+    assert one_launch_a_solve(2) and S.given_up() == 0
+    for pause in (64, 128):
+        assert S.L.gea_set_wait_limit(S.ctx, 0) == 0
+        assert not one_launch_a_solve(1)  # (tried, done again: the first of the pause)
+        assert S.L.gea_set_wait_limit(S.ctx, 25000000) == 0
+        n = S.given_up()
+        assert n == (1 if pause == 64 else 2)
+        assert not one_launch_a_solve(1)
+        S.step(pause - 4)
+        assert not one_launch_a_solve(1)  # (the last of it: step number pause - 1, the try being one)
+        assert one_launch_a_solve(2) and S.given_up() == n
+    S.close()
