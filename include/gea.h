@@ -331,6 +331,14 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
                                      const double* b, double* x, double tol, int32_t max_iter,
                                      void* hip_stream, gea_solve_stats* stats);
 
+/* Test support: the same with the wait limit of gea_set_wait_limit; given_up:
+ * host, 1 if the one-launch solve was given up and the system solved with one
+ * launch an iteration instead, else 0. */
+gea_status gea_pressure_solve_static_wait(const gea_mesh* mesh, const double* c, const double* D,
+                                          const double* b, double* x, double tol, int32_t max_iter,
+                                          void* hip_stream, uint64_t ticks, int32_t* given_up,
+                                          gea_solve_stats* stats);
+
 /* Release the context (the workspace stays with its owner). */
 void gea_destroy(gea_ctx* ctx);
 

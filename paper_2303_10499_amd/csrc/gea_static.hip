@@ -67,12 +67,16 @@ hipError_t static_area(double** out) {
 
 // 1/diag of the operator, diag = c + sum_f w_f, w_f = (D_P + D_N)/2 S_f/d_f,
 // summed in the order the right-hand-side kernels use (x, y: upper then
-// lower face; then z: upper, lower), so the result is theirs bitwise.
+// lower face; then z: upper, lower), so the result is theirs bitwise.  x0
+// given: keeps the initial guess x there.
 __global__ __launch_bounds__(kBlock) void k_static_diag_inv(Geo G, const double* __restrict__ c,
                                                             const double* __restrict__ D,
-                                                            double* __restrict__ dinv) {
+                                                            double* __restrict__ dinv,
+                                                            const double* __restrict__ x,
+                                                            double* __restrict__ x0) {
   const int Z = G.ndim - 1;
   for (int P = blockIdx.x * blockDim.x + threadIdx.x; P < G.nc; P += gridDim.x * blockDim.x) {
+    if (x0) x0[P] = x[P];
     const double Dc = D[P];
     double diag = c[P];
     for (int d = 0; d < Z; ++d) {
@@ -106,16 +110,15 @@ __global__ __launch_bounds__(kBlock) void k_static_fill(long n, double* __restri
 
 using namespace gea;
 
-extern "C" {
-
-gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, const double* D,
-                                     const double* b, double* x, double tol, int32_t max_iter,
-                                     void* hip_stream, gea_solve_stats* stats) {
+// spin: limit of a one-launch solve's waits; *given_up: it was given up
+static gea_status solve_static(const gea_mesh* mesh, const double* c, const double* D, const double* b,
+                               double* x, double tol, int32_t max_iter, void* hip_stream, uint64_t spin,
+                               int32_t* given_up, gea_solve_stats* stats) {
   auto fail = [](gea_status st, const std::string& msg) {
     set_call_error(msg);
     return st;
   };
-  if (!mesh || !c || !D || !b || !x || !stats) return fail(GEA_ERR_ARG, "null argument");
+  if (!mesh || !c || !D || !b || !x || !given_up || !stats) return fail(GEA_ERR_ARG, "null argument");
   if (mesh->nx < 1 || mesh->ny < 1 || mesh->nz < 1 || !(mesh->lx > 0) || !(mesh->ly > 0) ||
       !(mesh->lz > 0))
     return fail(GEA_ERR_ARG, "non-positive mesh size");
@@ -136,6 +139,7 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
                              "than its static work area holds");
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   *stats = gea_solve_stats{};
+  *given_up = 0;
   auto hip_fail = [&](hipError_t e, const char* what) {
     char buf[200];
     std::snprintf(buf, sizeof buf, "HIP error %d (%s) in %s", (int)e, hipGetErrorString(e), what);
@@ -160,17 +164,19 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
   w.b = setup_parts + 2L * kMaxZBlocks;
   w.sc = sc;
   CgVectors<double> v{x, vec[0], vec[1], vec[2], vec[3], vec[4], vec[5], c, D, vec[6], b};
-  // the scalars keep the last call's values: clear them (a fill kernel, no
-  // memset node), then 1/diag and the solve's set-up
-  hipLaunchKernelGGL(k_static_fill, dim3(1), dim3(kBlock), 0, s,
-                     (long)(sizeof(CgScalars) / sizeof(double)), reinterpret_cast<double*>(sc), 0.0);
-  hipLaunchKernelGGL(k_static_diag_inv, dim3(grid_for(G.nc)), dim3(kBlock), 0, s, G, c, D, vec[6]);
-  cg_init<double>(s, G, v, w, tol, max_iter);
   // the whole solve in one launch where the mesh has a plan for it (its
   // exchange area: zero from the start, its words tagged from launch to launch)
   const CgpPlan plan = cgp_plan<double>(G, false);
   uint64_t* const ex = reinterpret_cast<uint64_t*>(sc) + kStaticScalarDoubles;
   const bool one = plan.variant && plan.words <= kStaticExchange;
+  double* const x0 = vec[1];  // (that launch uses r and 1/diag of the vectors)
+  // the scalars keep the last call's values: clear them (a fill kernel, no
+  // memset node), then 1/diag and the solve's set-up
+  hipLaunchKernelGGL(k_static_fill, dim3(1), dim3(kBlock), 0, s,
+                     (long)(sizeof(CgScalars) / sizeof(double)), reinterpret_cast<double*>(sc), 0.0);
+  hipLaunchKernelGGL(k_static_diag_inv, dim3(grid_for(G.nc)), dim3(kBlock), 0, s, G, c, D, vec[6],
+                     (const double*)x, one ? x0 : nullptr);
+  cg_init<double>(s, G, v, w, tol, max_iter);
   int dev = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e, "hipGetDevice");
   struct Share {
@@ -184,7 +190,7 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
   if (one) {
     card_take(dev, plan.share);
     share.n = plan.share;
-    cgp_solve<double>(s, G, v, plan, ex, kCgpSpin, sc);
+    cgp_solve<double>(s, G, v, plan, ex, spin, sc);
   }
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "solve set-up");
   CgScalars hs;
@@ -195,7 +201,11 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
   if ((e = read()) != hipSuccess) return hip_fail(e, "reading the solver scalars");
   if (hs.status == kCgpAborted) {
     // its workgroups were not on the card together: clear the area and solve
-    // with the iteration kernels from the x it left
+    // with the iteration kernels from the initial guess (workgroups that ended
+    // well beside the one that gave up have written their part of x)
+    *given_up = 1;
+    if ((e = hipMemcpyAsync(x, x0, sizeof(double) * G.nc, hipMemcpyDeviceToDevice, s)) != hipSuccess)
+      return hip_fail(e, "restoring x");
     hipLaunchKernelGGL(k_static_fill, dim3(grid_for((int)kStaticExchange)), dim3(kBlock), 0, s,
                        kStaticExchange, reinterpret_cast<double*>(ex), 0.0);
     cg_init<double>(s, G, v, w, tol, max_iter);
@@ -245,6 +255,22 @@ gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, cons
     set_call_error(stats->status == GEA_ERR_NOCONV ? "gea_pressure_solve_static: no convergence"
                                                    : "gea_pressure_solve_static: non-finite value");
   return (gea_status)stats->status;
+}
+
+extern "C" {
+
+gea_status gea_pressure_solve_static(const gea_mesh* mesh, const double* c, const double* D,
+                                     const double* b, double* x, double tol, int32_t max_iter,
+                                     void* hip_stream, gea_solve_stats* stats) {
+  int32_t given_up = 0;
+  return solve_static(mesh, c, D, b, x, tol, max_iter, hip_stream, kCgpSpin, &given_up, stats);
+}
+
+gea_status gea_pressure_solve_static_wait(const gea_mesh* mesh, const double* c, const double* D,
+                                          const double* b, double* x, double tol, int32_t max_iter,
+                                          void* hip_stream, uint64_t ticks, int32_t* given_up,
+                                          gea_solve_stats* stats) {
+  return solve_static(mesh, c, D, b, x, tol, max_iter, hip_stream, ticks, given_up, stats);
 }
 
 }  // extern "C"

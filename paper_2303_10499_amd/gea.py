@@ -105,6 +105,8 @@ def lib():
         L.gea_state_extrema.argtypes = [vp, P(Extrema)]
         L.gea_pressure_solve_static.argtypes = [P(Mesh), dp, dp, dp, dp, C.c_double, C.c_int32,
                                                 vp, P(SolveStats)]
+        L.gea_pressure_solve_static_wait.argtypes = [P(Mesh), dp, dp, dp, dp, C.c_double, C.c_int32,
+                                                     vp, C.c_uint64, P(C.c_int32), P(SolveStats)]
         L.gea_destroy.argtypes = [vp]
         L.gea_destroy.restype = None
         L.gea_last_error.argtypes = [vp]
@@ -114,7 +116,8 @@ def lib():
                      "gea_apply_pressure_operator", "gea_get_fields", "gea_kernel_timing",
                      "gea_kernel_times", "gea_time_solver_kernels", "gea_time_network",
                      "gea_pressure_solve_static", "gea_state_extrema", "gea_set_face_flux",
-                     "gea_set_history", "gea_set_wait_limit", "gea_given_up"):
+                     "gea_set_history", "gea_set_wait_limit", "gea_given_up",
+                     "gea_pressure_solve_static_wait"):
             getattr(L, name).restype = C.c_int
         _lib = L
     return _lib

@@ -130,3 +130,42 @@ def test_one_launch_solves_come_back(oracle_lib, gea_mod, dims):  # noqa: F811
         assert not one_launch_a_solve(1)  # (the last of it: step number pause - 1, the try being one)
         assert one_launch_a_solve(2) and S.given_up() == n
     S.close()
+
+
+# The static solve: done again from the initial guess (workgroups that ended well
+# beside the one that gave up have written their part of x), with nothing left
+# for the next call.
+@pytest.mark.parametrize("dims", [(333, 0, 251), (60, 50, 40)])
+def test_a_given_up_static_solve_is_done_again(oracle_lib, gea_mod, dims):  # noqa: F811
+    import ctypes as C
+
+    import torch
+    tol = 1e-11
+    O, s, S, cfg = context(oracle_lib, gea_mod, dims, "pcg64", tol=1e-9)
+    S.step(1)
+    x0 = S.state()["pp"]
+    S.pressure_solve(np.ascontiguousarray(x0))
+    c, D, b = S.get_fields(gea_mod.FIELD_C | gea_mod.FIELD_D | gea_mod.FIELD_B)
+    mesh, L = S.mesh, S.L
+    S.close()
+    dev = [torch.tensor(v, device="cuda:0") for v in (c, D, b)]
+
+    def solve(ticks):
+        x, st, n = torch.tensor(x0, device="cuda:0"), gea_mod.SolveStats(), C.c_int32(-1)
+        rc = L.gea_pressure_solve_static_wait(C.byref(mesh), *[C.c_void_p(t.data_ptr()) for t in (*dev, x)], tol, 20000,
+                                              C.c_void_p(torch.cuda.current_stream().cuda_stream), ticks, C.byref(n),
+                                              C.byref(st))
+        assert rc == gea_mod.OK
+        x = x.cpu().numpy()
+        assert np.linalg.norm(b - O.apply_A(c, D, x)) <= 1.1 * tol * np.linalg.norm(b)
+        return x, st, n.value
+
+    x1, st1, n1 = solve(25000000)
+    assert n1 == 0
+    x2, st2, n2 = solve(0)
+    assert n2 == 1 and st2.rel_res0 == st1.rel_res0 and abs(st2.iters - st1.iters) <= 1
+    for _ in range(4):
+        x, st, n = solve(0)
+        assert n == 1 and st.iters == st2.iters and np.array_equal(x, x2)
+    x, st, n = solve(25000000)
+    assert n == 0 and st.iters == st1.iters and np.array_equal(x, x1)
