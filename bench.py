@@ -45,6 +45,13 @@ ALG_BYTES_PER_CELL = {0: 120.0, 2: 60.0}
 # What the fused iteration kernel itself must move: 11 arrays (read r, A p,
 # p, x, 1/diag, c, D; write r, p, A p, x).
 FUSED_BYTES_PER_CELL = {0: 88.0, 2: 44.0}
+# A one-launch solve (where the mesh's vectors fit the chip) moves, once a
+# launch, r, x, c, D, 1/diag in and x out (the FP32 inner solve: the FP64 outer
+# iterate in and out instead of x); and each iteration nothing, but with x, c
+# and D left in memory (3D FP32 meshes of more than 256 tiles of 64 x 16 x 16
+# cells, whose launch reads r and 1/diag, then x once more at its end) D, c, x
+# in and x out.
+ONE_LAUNCH_BYTES_PER_CELL = {0: (48.0, 0.0), 2: (36.0, 0.0), "memory": (28.0, 16.0)}
 CLASS_NAMES = {0: "k_cg_iter<fp64>", 1: "k_cg_scalars<fp64>", 2: "k_cg_iter<fp32>",
                3: "k_cg_scalars<fp32>", 4: "solver set-up kernels",
                5: "explicit step kernels", 6: "learned network", 7: "energy solve kernels"}
@@ -97,6 +104,29 @@ def make_solver(cfg, form):
     return S
 
 
+def cg_candidate(mesh, it_class, kms, kn, avg, iters_per_step, solves_per_step, kernel_steps):
+    """the roofline candidate of the pressure solves' CG kernel, by class (0
+    FP64, 2 FP32): the iteration kernel, or, where no scalar kernel went out
+    behind one, the one-launch solve.  That one is given by the iteration: its
+    event-timed device time and what it has to move, set-up and end shared out
+    (the learned forms' class holds their flexible-CG step too).
+    solves_per_step: solves that iterated."""
+    nc = mesh["nx"] * mesh["ny"] * mesh["nz"]
+    if kn[it_class] == 0 or kn[it_class + 1] > 0 or iters_per_step == 0:
+        return CLASS_NAMES[it_class], dict(
+            bound="hbm", avg_ms=avg[it_class], per_step_ms=avg[it_class] * iters_per_step,
+            bytes_alg=ALG_BYTES_PER_CELL[it_class] * nc, bytes_fused=FUSED_BYTES_PER_CELL[it_class] * nc,
+            per_cell=(ALG_BYTES_PER_CELL[it_class], FUSED_BYTES_PER_CELL[it_class]))
+    tiles = -(-mesh["nx"] // 64) * -(-mesh["ny"] // 16) * -(-mesh["nz"] // 16)
+    in_memory = it_class == 2 and mesh["ny"] > 1 and tiles > 256
+    launch, iteration = ONE_LAUNCH_BYTES_PER_CELL["memory" if in_memory else it_class]
+    per_cell = iteration + launch * solves_per_step / iters_per_step
+    per_step_ms = kms[it_class] / kernel_steps
+    return "k_cgp%d<%s>" % (2 if mesh["ny"] == 1 else 3, "fp64" if it_class == 0 else "fp32"), dict(
+        bound="hbm", avg_ms=per_step_ms / iters_per_step, per_step_ms=per_step_ms, per="iteration of a one-launch solve",
+        bytes_alg=per_cell * nc, bytes_fused=per_cell * nc, per_cell=(per_cell, per_cell))
+
+
 def run_window(cfg, form, steps, warmup, kernel_steps):
     """the timed window of a form, its kernel accounting and roofline candidates"""
     solver, lsteps, _ = FORMS[form]
@@ -122,20 +152,22 @@ def run_window(cfg, form, steps, warmup, kernel_steps):
     kms, kn = S.kernel_times()
     S.kernel_timing(False)
     iters_per_step = st_k.total_iters / kernel_steps
-    avg = S.time_solver_kernels(reps=50)   # back-to-back launches between two events
+    # back-to-back launches between two events (of the iteration kernels, also
+    # on a mesh whose solves take one launch)
+    avg = S.time_solver_kernels(reps=50)
     out["kernel_avg_us"] = {CLASS_NAMES[k]: round(avg[k] * 1e3, 2) for k in range(4)}
-    out["launches_per_step"] = {CLASS_NAMES[k]: kn[k] / kernel_steps for k in range(8) if kn[k]}
     out["energy_iters_per_step"] = st_k.energy_iters / kernel_steps
     out["energy_ms_per_step_event_timed"] = kms[7] / kernel_steps
     out["iterations_per_step"] = iters_per_step
     out["explicit_ms_per_step_event_timed"] = kms[5] / kernel_steps
     cands = {}
     it_class = 0 if solver == "pcg64" else 2
-    cands[CLASS_NAMES[it_class]] = dict(bound="hbm", avg_ms=avg[it_class],
-                                        per_step_ms=avg[it_class] * iters_per_step,
-                                        bytes_alg=ALG_BYTES_PER_CELL[it_class] * nc,
-                                        bytes_fused=FUSED_BYTES_PER_CELL[it_class] * nc,
-                                        per_cell=(ALG_BYTES_PER_CELL[it_class], FUSED_BYTES_PER_CELL[it_class]))
+    # (of the last step, as the refined forms' inner solves are counted a solve)
+    solves = sum(max(s.outer_iters, 1) for s in st_k.solve[:st_k.n_solves] if s.iters > 0)
+    name, cand = cg_candidate(cfg["mesh"], it_class, kms, kn, avg, iters_per_step, solves, kernel_steps)
+    cands[name] = cand
+    out["launches_per_step"] = {name if k == it_class else CLASS_NAMES[k]: kn[k] / kernel_steps
+                                for k in range(8) if kn[k]}
     if solver == "learned":
         nms, ngf = S.time_network(reps=20)
         apps = kn[6] / kernel_steps
@@ -200,7 +232,7 @@ def roofline_entry(rr):
     if rr["bound"] == "hbm":
         achieved = rr["bytes_alg"] / t / 1e9
         fused = rr["bytes_fused"] / t / 1e9
-        return dict(bound="hbm", kernel=rr["kernel"], achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
+        return dict(bound="hbm", kernel=rr["kernel"], **({"per": rr["per"]} if "per" in rr else {}), achieved=round(achieved, 1), peak=HBM_PEAK_GBS,
                     unit="GB/s", frac=round(achieved / HBM_PEAK_GBS, 4),
                     avg_launch_us=round(rr["avg_ms"] * 1e3, 2),
                     bytes_per_cell=rr["per_cell"][0], bytes_per_launch=rr["bytes_alg"],
@@ -356,7 +388,8 @@ def main():
         also = {"workload": cfg2["name"],
                 "cells": cfg2["mesh"]["nx"] * cfg2["mesh"]["ny"] * cfg2["mesh"]["nz"],
                 "forms": public(res2), "speedup_vs_pcg64": speedups(res2),
-                "roofline": {k: roofline_entry(v["_roofline"]) for k, v in res2.items()},
+                # (the traffic counters are those of the first mesh)
+                "roofline": {k: dict(roofline_entry(v["_roofline"]), traffic=None) for k, v in res2.items()},
                 "full_run": full2,
                 "implicit_transport": None if args.no_transport else
                 run_transport(cfg2, args.steps, args.warmup)}
