@@ -932,6 +932,7 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     if (unread) {  // the inner solve enqueued unread, and the check before it
       unread = false;
       x->note_conv(unread_outer, s_res.done != 0);
+      if (s_res.done) --outer;  // (nothing was left to refine)
       if (out->rel_res0 < 0) out->rel_res0 = s_res.bb > 0 ? std::sqrt(s_res.rr / s_res.bb) : 0.0;
       check_cgp(x, s_cg);
       total += s_cg.iter;
@@ -1168,6 +1169,7 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
       unread = false;
       unread_bound = 0;
       x->note_conv(0, s_res.done != 0);
+      if (s_res.done) --outer;  // (as in solve_mixed)
       if (out->rel_res0 < 0) out->rel_res0 = s_res.bb > 0 ? std::sqrt(s_res.rr / s_res.bb) : 0.0;
       check_cgp(x, s_cg);
       total += s_cg.iter + s_fcg.iter;
