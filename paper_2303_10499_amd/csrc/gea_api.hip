@@ -847,6 +847,12 @@ gea_status solve_pcg64(gea_ctx* x, double* xv, gea_solve_stats* out) {
   return (gea_status)out->status;
 }
 
+// b = 0 in a refined solve: x = 0
+void clear_solution(gea_ctx* x, double* xv, gea_solve_stats* out) {
+  HIPCHK(hipMemsetAsync(xv, 0, sizeof(double) * x->G.nc, x->stream));
+  out->rel_res = 0.0;
+}
+
 // FP64 outer residual + FP32 inner Jacobi-PCG on the correction.
 // An inner solve goes out unread behind its residual check when the same
 // check did not converge last step and the solve's length is known: a batch
@@ -932,9 +938,13 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
     if (unread) {  // the inner solve enqueued unread, and the check before it
       unread = false;
       x->note_conv(unread_outer, s_res.done != 0);
-      if (s_res.done) --outer;  // (nothing was left to refine)
+      if (s_res.done || s_res.bb == 0.0) --outer;  // (nothing was left to refine)
       if (out->rel_res0 < 0) out->rel_res0 = s_res.bb > 0 ? std::sqrt(s_res.rr / s_res.bb) : 0.0;
       check_cgp(x, s_cg);
+      if (s_res.bb == 0.0) {  // b = 0: x = 0, whatever that solve made of it
+        clear_solution(x, xv, out);
+        break;
+      }
       total += s_cg.iter;
       time_whole(s_cg.iter);
       if (s_cg.status == -5) {
@@ -969,8 +979,7 @@ gea_status solve_mixed(gea_ctx* x, double* xv, gea_solve_stats* out) {
       break;
     }
     if (h64.bb == 0.0) {
-      HIPCHK(hipMemsetAsync(xv, 0, sizeof(double) * G.nc, x->stream));
-      out->rel_res = 0.0;
+      clear_solution(x, xv, out);
       break;
     }
     if (h64.done) {
@@ -1169,9 +1178,13 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
       unread = false;
       unread_bound = 0;
       x->note_conv(0, s_res.done != 0);
-      if (s_res.done) --outer;  // (as in solve_mixed)
+      if (s_res.done || s_res.bb == 0.0) --outer;  // (as in solve_mixed)
       if (out->rel_res0 < 0) out->rel_res0 = s_res.bb > 0 ? std::sqrt(s_res.rr / s_res.bb) : 0.0;
       check_cgp(x, s_cg);
+      if (s_res.bb == 0.0) {  // (as in solve_mixed)
+        clear_solution(x, xv, out);
+        break;
+      }
       total += s_cg.iter + s_fcg.iter;
       x->last_iters_res = s_cg.iter;
       if (s_fcg.status == 1) ++fallbacks;  // stalled: Jacobi-PCG took over
@@ -1208,8 +1221,7 @@ gea_status solve_learned(gea_ctx* x, double* xv, gea_solve_stats* out) {
       break;
     }
     if (h64.bb == 0.0) {
-      HIPCHK(hipMemsetAsync(xv, 0, sizeof(double) * G.nc, x->stream));
-      out->rel_res = 0.0;
+      clear_solution(x, xv, out);
       break;
     }
     if (h64.done) {
