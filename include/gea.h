@@ -264,7 +264,7 @@ gea_status gea_get_fields(gea_ctx* ctx, uint32_t field_mask, double* out, gea_pt
  *     that iteration's partials, except at the start of a batch of
  *     iterations; the previous update of r and x, the new direction p,
  *     q = A p, the iteration's partial dot products)
- *     or, on 2D meshes whose tiles fit the card, the whole solve in one launch
+ *     or, on meshes whose tiles fit the card, the whole solve in one launch
  *   1 FP64 CG scalar kernel (one workgroup, at the end of each batch:
  *     alpha, beta, stop test)
  *   2 FP32 inner CG iteration kernel (or whole inner solve)  3 FP32 inner CG scalar kernel
@@ -316,7 +316,10 @@ gea_status gea_given_up(gea_ctx* ctx, int64_t* count);
  * passes, with every work vector, partial sum and solver scalar in one
  * static device array of the library (about 70 MB per GPU, held from the
  * first call on a device until the process ends).  It allocates nothing
- * and needs no context.
+ * and needs no context.  The solve is one launch where the mesh's tiles fit
+ * the card and what they exchange fits the array, which in 3D is so up to
+ * 232 tiles of 64 x 8 x 2 cells, else (above 256 of those) 191 of 64 x 8 x 4,
+ * else 140 of 64 x 8 x 8; larger systems take one launch an iteration.
  *   mesh: at most 2^20 cells (GEA_ERR_ARG beyond, see gea_last_error(NULL));
  *   c, D, b: ncell device values of the system c_i x_i + sum_f w_f (x_i -
  *     x_nb) = b_i, w_f = (D_P + D_N)/2 S_f/d_f (as gea_get_fields returns

@@ -25,10 +25,10 @@
 // L2s: about 3 us an iteration up to 50 workgroups, 5 us at 250), on large
 // ones the FP64 sums and the stencil on the vector units.  One iteration
 // (with its share of the solve's set-up), us, one launch an iteration
-// before / now: 64 x 32 FP64 25 / 4.5 (one workgroup, 2.4 without the set-up),
-// 200 x 200 FP64 15.7 / 4.1, 333 x 251 15.9 / 4.4, 1024 x 1024 26.8 / 6.5,
-// 2048 x 2048 FP32 33 / 11.4 (its 11 arrays a cell came from the last-level
-// cache at 5.8 TB/s).  A workgroup's sums are one 128-byte line, read by
+// before / now: 64 x 32 FP64 25 / 4.5 (one workgroup: the launch takes 8 and
+// 1.5 an iteration), 200 x 200 FP64 15.7 / 4.1, 333 x 251 15.9 / 4.4,
+// 1024 x 1024 26.8 / 6.5, 2048 x 2048 FP32 33 / 11.4 (its 11 arrays a cell came
+// from the last-level cache at 5.8 TB/s).  A workgroup's sums are one 128-byte line, read by
 // coalesced loads of four: as 14 rows of one word a workgroup, which all
 // workgroups polled at once, 1024 x 1024 took 11.5 us.  The registers decide
 // how many rows a thread can hold (R = 32 in FP32 at two waves a SIMD): the

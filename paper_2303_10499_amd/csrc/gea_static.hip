@@ -28,7 +28,13 @@ constexpr int kStaticVectors = 7;             // r, r1, p0, p1, q, q1, 1/diag
 constexpr long kStaticIterParts = 7L * 65536;  // 7 partials per iteration-kernel workgroup, two parity sets
 constexpr long kStaticSetupParts = 3L * kMaxZBlocks;  // set-up: 2 + 1 per workgroup
 constexpr long kStaticScalarDoubles = 32;     // one CgScalars (256 bytes)
-constexpr long kStaticExchange = 1228800;     // words of the one-launch solve's exchange area
+// Words of the one-launch solve's exchange area: those of any 2D plan (512
+// workgroups of at most 2336 words each).  A 3D tile's border takes more: 232
+// tiles of 64 x 8 x 2 cells fit, 191 of 64 x 8 x 4, 140 of 64 x 8 x 8, 92 of
+// 64 x 16 x 8.  A mesh whose plan needs more (96 x 96 x 48 cells: 144 tiles of
+// 64 x 8 x 8) takes the iteration kernels, though a context on it solves in one
+// launch.
+constexpr long kStaticExchange = 1228800;
 constexpr long kStaticDoubles = kStaticVectors * kStaticMaxCells + kStaticIterParts +
                                 kStaticSetupParts + kStaticScalarDoubles + kStaticExchange;
 static_assert(sizeof(CgScalars) <= kStaticScalarDoubles * sizeof(double), "scalar slot");

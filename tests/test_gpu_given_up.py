@@ -169,3 +169,29 @@ def test_a_given_up_static_solve_is_done_again(oracle_lib, gea_mod, dims):  # no
         assert n == 1 and st.iters == st2.iters and np.array_equal(x, x2)
     x, st, n = solve(25000000)
     assert n == 0 and st.iters == st1.iters and np.array_equal(x, x1)
+
+
+# A static mesh whose exchange does not fit the static area (96 x 96 x 48: 144
+# tiles of 64 x 8 x 8) takes the iteration kernels.
+def test_static_mesh_above_the_exchange_area(gea_mod):  # noqa: F811
+    import ctypes as C
+
+    import torch
+    mesh = gea_mod.make_mesh(dict(nx=96, ny=96, nz=48, lx=960.0, ly=960.0, lz=480.0))
+    n = 96 * 96 * 48
+    b = torch.rand(n, generator=torch.Generator().manual_seed(3), dtype=torch.float64).cuda()
+    c, D, x = torch.full_like(b, 0.01), torch.full_like(b, 0.01), torch.zeros_like(b)
+    st, up = gea_mod.SolveStats(), C.c_int32(-1)
+    rc = gea_mod.lib().gea_pressure_solve_static_wait(
+        C.byref(mesh), *[C.c_void_p(t.data_ptr()) for t in (c, D, b, x)], 1e-10, 20000,
+        C.c_void_p(torch.cuda.current_stream().cuda_stream), 0, C.byref(up), C.byref(st))
+    assert rc == gea_mod.OK and st.rel_res <= 1e-10 and st.iters > 1
+    assert up.value == 0  # (no one-launch solve that could give up)
+    # the residual with a uniform D: c x + D (S/h) (differences to the neighbours)
+    v = x.view(48, 96, 96)
+    r = b.view(48, 96, 96) - 0.01 * v
+    for d in range(3):
+        f = 0.01 * 10.0 * (v.narrow(d, 1, v.shape[d] - 1) - v.narrow(d, 0, v.shape[d] - 1))
+        r.narrow(d, 0, v.shape[d] - 1).add_(f)
+        r.narrow(d, 1, v.shape[d] - 1).sub_(f)
+    assert float(r.norm() / b.norm()) <= 1.1e-10
